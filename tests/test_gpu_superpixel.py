@@ -97,6 +97,25 @@ def test_superpixel_edge_cases():
     _compare_whole(f1, m1, s1, fb1, 3, 0.2)
 
 
+@pytest.mark.parametrize("W,H,N,K,iters", [
+    (48, 30, 3000, 2100, 3),     # more candidates than a tile's LDS pool holds
+    (33, 9, 60, 42, 3),          # one pixel beyond a tile in x and in y
+    (70, 41, 1400, 980, 2),      # S = 1: the largest window of cells
+    (300, 200, 12, 8, 4)])       # S larger than a tile
+def test_superpixel_tile_edges(W, H, N, K, iters):
+    print(f"superpixel tile edges {W}x{H} K={K}", flush=True)
+    frame, mask, seeds, fb = _inputs(W, H, N, seed=21)
+    assert len(seeds) == K
+    _compare_whole(frame, mask, seeds, fb, iters, 0.1)
+    # without the optional outputs the Gaussians are the same
+    _, _, gx, gc, gr = _gpu(frame, mask, seeds, fb, iters, 0.1)
+    xy, chol, rgb = (dev(np.ascontiguousarray(a, F32)) for a in fb)
+    _lib.init_superpixel(dev(frame), dev(mask.astype(np.uint8)), dev(seeds), xy, chol, rgb,
+                         iters=iters, compactness=0.1)
+    for a, b in ((xy, gx), (chol, gc), (rgb, gr)):
+        np.testing.assert_array_equal(host(a), b)
+
+
 def _window_labels(frame, roi, cx, cy, cc, S, w, k):
     """The oracle's labels of every pixel of centre k's 3S x 3S window."""
     H, W = roi.shape

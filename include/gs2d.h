@@ -393,7 +393,7 @@ size_t gs2d_init_workspace_bytes(int32_t W, int32_t H);
  *   draws (caller-supplied);
  *   outputs xy [N][2], chol [N][3], rgb [N][3] with N = n_roi + n_out, ROI
  *   draws first; picked [N] int32 (nullable) receives each draw's pixel index.
- * Synchronises `stream` once (reads the region totals) before the last launch. */
+ * Enqueued on `stream` without synchronising (no host reads). */
 int gs2d_init_plain(int32_t W, int32_t H, const float *target, const uint8_t *roi_mask,
                     int32_t n_roi, const int64_t *pick_roi, const float *jit_roi, int32_t n_out,
                     const int64_t *pick_out, const float *jit_out, float *xy, float *chol,

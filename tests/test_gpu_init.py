@@ -52,3 +52,15 @@ def test_init_full_hd():
     print("init 1080p", flush=True)
     frame, mask = synth.make_frame(1920, 1080, seed=201)
     _compare(frame, mask, synth.init_draws(30000, seed=202))
+
+
+@pytest.mark.parametrize("W,H,N", [
+    (7, 5, 40),          # less than one group of pixels
+    (1, 70, 33),         # one column
+    (65, 63, 300),       # the last group ragged, two chunks
+    (2500, 1000, 400)])  # chunks of more than one batch of groups
+def test_init_group_and_chunk_edges(W, H, N):
+    print(f"init {W}x{H} N={N}", flush=True)
+    frame, mask = synth.make_frame(W, H, seed=31)
+    mask[0, 0] = True
+    _compare(frame, mask, synth.init_draws(N, seed=32))

@@ -103,6 +103,53 @@ def test_targets_match_oracle():
     assert counts.max() == 8 and counts.sum() > 300
 
 
+def _serial_targets(xy, chol, rgb, Wf, TX):
+    """Kept indices per tile by the definition: members in index order, a
+    ninth replaces the lightest kept one if it is heavier (comparisons with
+    NaN are false)."""
+    f = np.float32
+    c = rgb.astype(f)
+    mass = np.abs(chol[:, 0] * chol[:, 2]) * ((c[:, 0] * c[:, 0] + c[:, 1] * c[:, 1])
+                                              + c[:, 2] * c[:, 2])
+    kept = {}
+    for n in range(len(xy)):
+        k = kept.setdefault(int(xy[n, 1] // 16) * TX + int(xy[n, 0] // 16), [])
+        if len(k) < 8:
+            k.append(n)
+            continue
+        w = 0
+        for j in range(1, 8):
+            if mass[k[j]] < mass[k[w]] or (mass[k[j]] == mass[k[w]] and k[j] > k[w]):
+                w = j
+        if mass[n] > mass[k[w]]:
+            k[w] = n
+    return {t: sorted(k) for t, k in kept.items()}
+
+
+@pytest.mark.parametrize("N,nan", [(60, False), (5000, False), (600, True), (5000, True)])
+def test_targets_of_full_tiles(N, nan):
+    """5000 Gaussians on 15 tiles: far more members than a wavefront has
+    lanes; equal masses; masses that are NaN."""
+    print(f"cnn targets full tiles N={N} nan={nan}", flush=True)
+    Hf, Wf = 40, 70
+    xy, chol, rgb = synth.random_gaussians(N, Wf, Hf, seed=16, scale_lo=0.6, scale_hi=3.0)
+    chol[::3] = chol[0]
+    rgb[::3] = rgb[0]
+    if nan:
+        rgb[5::40, 1] = np.nan
+    net = _lib.CNNInit(Hf, Wf, seed=5)
+    net.set_targets(dev(xy), dev(chol), dev(rgb))
+    counts, vec = (host(t) for t in net.read_targets())
+    ref = _serial_targets(xy, chol, rgb, Wf, net.TX)
+    for t in range(net.TY * net.TX):
+        ids = ref.get(t, [])
+        assert counts[t] == len(ids), t
+        np.testing.assert_array_equal(vec[t, :len(ids), 5:], rgb[ids])
+        np.testing.assert_array_equal(vec[t, :len(ids), 3], chol[ids, 1])
+        np.testing.assert_allclose(vec[t, :len(ids), 2], np.log(chol[ids, 0]), rtol=1e-5, atol=1e-5)
+        assert not vec[t, len(ids):].any()
+
+
 # 288 x 352: layer 0's 144 x 176 outputs make 50 pixel splits of the grad-
 # weight GEMM, so its partial tiles are summed in two chunks (combined with
 # atomics), as at full resolution

@@ -12,7 +12,7 @@
 // Optionally the kernel clears the gradients after reading them (ready for
 // the next backward pass's atomics), and block 0 reduces the per-tile loss
 // partials of this iteration into loss_trace[t-1].
-#include "gs2d_internal.h"
+#include "quant_common.h"
 
 namespace gs2d {
 
@@ -72,6 +72,63 @@ k_adam(int N, float *__restrict__ xy, float *__restrict__ chol, float *__restric
       }
     }
   }
+}
+
+// The optimiser step of quantisation-aware fitting, one thread per Gaussian:
+// Adam on its 8 parameters (gradients cleared) and the block's extremes of
+// the updated Cholesky vectors and colours, from which the next iteration's
+// quantisers follow.  The last block reduces the loss partials.
+__global__ void __launch_bounds__(QB)
+k_adam_extremes(int N, PendingAdam a, float *__restrict__ part, int32_t *__restrict__ report) {
+  __shared__ double red[QB / 64];
+  const int t = a.step[0];
+  if (blockIdx.x == gridDim.x - 1) {
+    double s = thread_sum_parts(a.loss_part, a.n_part);
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double tot = 0.0;
+      for (int w = 0; w < QB / 64; ++w) tot += red[w];
+      const float loss = (float)(tot * (double)a.loss_scale);
+      if (t - 1 < a.trace_len) a.trace[t - 1] = loss;
+      if (report) {
+        report[0] = t;
+        report[1] = __float_as_int(loss);
+      }
+    }
+    return;
+  }
+  float bc1, bc2;
+  adam_bias(t, a.cfg.beta1, a.cfg.beta2, &bc1, &bc2);
+  float mn[6], mx[6];
+#pragma unroll
+  for (int c = 0; c < 6; ++c) mn[c] = INFINITY, mx[c] = -INFINITY;
+  const int n = blockIdx.x * QB + (int)threadIdx.x;
+  if (n < N) {
+    const bool upd = !a.active || a.active[n];
+    auto update = [&](float *p, float *g, size_t i, size_t o, float lr) {
+      const float gr = g[i];
+      g[i] = 0.f;
+      float x = p[i];
+      if (upd) {
+        x = adam_update(x, gr, a.m + o + i, a.v + o + i, lr, a.cfg.beta1, a.cfg.beta2, a.cfg.eps,
+                        bc1, bc2);
+        p[i] = x;
+      }
+      return x;
+    };
+    const size_t N2 = 2 * (size_t)N, N5 = 5 * (size_t)N;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) update(a.xy, a.g_xy, 2 * (size_t)n + c, 0, a.cfg.lr[0]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      mn[c] = mx[c] = update(a.chol, a.g_chol, 3 * (size_t)n + c, N2, a.cfg.lr[1]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      mn[3 + c] = mx[3 + c] = update(a.rgb, a.g_rgb, 3 * (size_t)n + c, N5, a.cfg.lr[2]);
+  }
+  block_extremes(mn, mx, part + blockIdx.x * 12);
 }
 
 __global__ void k_step_tick(int32_t *__restrict__ step) {
@@ -146,6 +203,13 @@ hipError_t launch_adam(int N, float *xy, float *chol, float *rgb, float *g_xy, f
                      g_rgb, m, v, step, cfg.lr[0], cfg.lr[1], cfg.lr[2], cfg.beta1, cfg.beta2,
                      cfg.eps, active, zero_grads, loss_part, n_loss_part, loss_scale, loss_trace,
                      trace_len, report);
+  return hipGetLastError();
+}
+
+hipError_t launch_adam_extremes(const PendingAdam &a, int N, float *part, int32_t *report,
+                                hipStream_t st) {
+  hipLaunchKernelGGL(k_adam_extremes, dim3((N + QB - 1) / QB + 1), dim3(QB), 0, st, N, a, part,
+                     report);
   return hipGetLastError();
 }
 

@@ -265,30 +265,45 @@ hipError_t enqueue_iterations(const Layout &L, void *ws, const float *target, fl
   // the start of a call unless the workspace holds complete lists of this
   // layout)
   const float skin = (L.wide && bin_skin > 0.f) ? bin_skin : 0.f;
+  const PendingAdam pending{xy,    chol, rgb,  g_xy, g_chol, g_rgb, m,         v,
+                            step,  cfg,  at<const float>(ws, L.loss_part), L.loss_parts,
+                            loss_scale, trace, trace_len, active};
   if (qat_bits_chol > 0) {
     // quantisation-aware: quantise, bin and render the quantised copy, then
     // Adam on the FP32 parameters with its gradients (straight through); the
-    // lazy lists follow the quantised Gaussians (the raster ticks the step)
+    // lazy lists follow the quantised Gaussians (the raster ticks the step).
+    // On the single-pass path the quantiser runs inside the projection, from
+    // the extremes that the optimiser step before left (the chunk's first
+    // iteration forms them itself).
     float *q = at<float>(ws, L.qparams);
     float *q_xy = q, *q_chol = q + 2 * (size_t)L.N, *q_rgb = q + 5 * (size_t)L.N;
+    void *qws = at<void>(ws, L.qws);
+    int n_parts = 0;
+    float *part = quant_parts(L.N, qws, &n_parts);
+    const PendingQuant quant{xy,   chol,    rgb,           q_rgb,
+                             part, n_parts, qat_bits_chol, qat_bits_rgb};
+    int32_t *report = at<int32_t>(ws, L.misc) + MISC_STEP;
     hipError_t e = hipSuccess;
+    if (L.wide && k > 0) e = launch_quant_extremes(L.N, chol, rgb, qws, st);
     for (int i = 0; i < k && e == hipSuccess; ++i) {
-      e = launch_quantise(L.N, xy, chol, rgb, qat_bits_chol, qat_bits_rgb, q_xy, q_chol, q_rgb,
-                          nullptr, nullptr, nullptr, at<void>(ws, L.qws), st);
-      if (e == hipSuccess) e = launch_binning(L, q_xy, q_chol, ws, st, step, nullptr, skin);
+      if (L.wide) {
+        e = launch_binning(L, nullptr, nullptr, ws, st, step, nullptr, skin, &quant);
+      } else {
+        e = launch_quantise(L.N, xy, chol, rgb, qat_bits_chol, qat_bits_rgb, q_xy, q_chol, q_rgb,
+                            nullptr, nullptr, nullptr, qws, st);
+        if (e == hipSuccess) e = launch_binning(L, q_xy, q_chol, ws, st, step, nullptr, skin);
+      }
       if (e == hipSuccess)
         e = launch_render_fused(L, ws, q_rgb, target, g_xy, g_chol, g_rgb, st, active, skin > 0.f,
                                 skin > 0.f ? step : nullptr);
       if (e == hipSuccess)
-        e = launch_adam(L.N, xy, chol, rgb, g_xy, g_chol, g_rgb, m, v, step, cfg, active, 1,
-                        at<const float>(ws, L.loss_part), L.loss_parts, loss_scale, trace,
-                        trace_len, st, at<int32_t>(ws, L.misc) + MISC_STEP);
+        e = L.wide ? launch_adam_extremes(pending, L.N, part, report, st)
+                   : launch_adam(L.N, xy, chol, rgb, g_xy, g_chol, g_rgb, m, v, step, cfg, active,
+                                 1, at<const float>(ws, L.loss_part), L.loss_parts, loss_scale,
+                                 trace, trace_len, st, report);
     }
     return e;
   }
-  const PendingAdam pending{xy,    chol, rgb,  g_xy, g_chol, g_rgb, m,         v,
-                            step,  cfg,  at<const float>(ws, L.loss_part), L.loss_parts,
-                            loss_scale, trace, trace_len, active};
   hipError_t e = hipSuccess;
   for (int i = 0; i < k && e == hipSuccess; ++i) {
     e = launch_binning(L, xy, chol, ws, st, step, i > 0 ? &pending : nullptr, skin);

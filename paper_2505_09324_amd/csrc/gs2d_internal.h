@@ -129,6 +129,16 @@ struct PendingAdam {
   const uint8_t *active;  // nullable: Gaussians with active[n] == 0 keep theta, m, v
 };
 
+// Quantisation-aware fitting: the quantisers of the FP32 parameters, applied
+// by the first binning kernel of an iteration to what it projects and to the
+// colours the raster reads (q_rgb), from the parameters' block extremes.
+struct PendingQuant {
+  const float *xy, *chol, *rgb;
+  float *q_rgb;
+  const float *part;  // [n_parts][12]
+  int n_parts, bits_chol, bits_rgb;
+};
+
 // Returns false if the shape is outside the supported limits.
 bool make_layout(const gs2d_shape &s, Layout *L);
 
@@ -169,9 +179,12 @@ inline T *at(void *ws, size_t off) {
 // identical.  The fused raster clears the flag and stamps a rebuild's lists
 // (launch_render_fused); exact binning clears the stamp.  The lazy path
 // does not tick step_tick: its caller ticks it in the raster.
+// quant (nullable, single-pass path only): project the quantised parameters
+// (xy and chol are not read) and write the quantised colours.
 hipError_t launch_binning(const Layout &L, const float *xy, const float *chol, void *ws,
                           hipStream_t st, int *step_tick = nullptr,
-                          const PendingAdam *adam = nullptr, float skin = 0.f);
+                          const PendingAdam *adam = nullptr, float skin = 0.f,
+                          const PendingQuant *quant = nullptr);
 
 // Raster (raster.hip).
 hipError_t launch_render_fwd(const Layout &L, void *ws, const float *rgb, const float *target,
@@ -201,6 +214,11 @@ hipError_t launch_adam(int N, float *xy, float *chol, float *rgb, float *g_xy, f
                        int n_loss_part, float loss_scale, float *loss_trace, int trace_len,
                        hipStream_t st, int32_t *report = nullptr);
 
+// The same step with the next quantisation's block extremes: part [ceil(N /
+// 256)][12] receives the extremes of the updated Cholesky vectors and colours.
+hipError_t launch_adam_extremes(const PendingAdam &a, int N, float *part, int32_t *report,
+                                hipStream_t st);
+
 hipError_t launch_fill_zero(float *p, size_t n, hipStream_t st);
 
 // Quantisation (quant.hip): binary16 means, uniform min-max codes of the
@@ -211,6 +229,10 @@ hipError_t launch_quantise(int N, const float *xy, const float *chol, const floa
                            uint16_t *codes, float *ranges, double *bits, void *qws,
                            hipStream_t st);
 size_t quantise_workspace_bytes(int N);
+// The first of its two launches alone, and where its block extremes are.
+hipError_t launch_quant_extremes(int N, const float *chol, const float *rgb, void *qws,
+                                 hipStream_t st);
+float *quant_parts(int N, void *qws, int *n_parts);
 hipError_t launch_fill_zero_u32(uint32_t *p, size_t n, hipStream_t st);
 // Start of a fitting call, in one launch: grads[0, n_grads) zeroed and misc
 // reset for the call.  With lazy binning, if the stamp (MISC_LISTS_LO/HI)

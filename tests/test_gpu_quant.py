@@ -90,3 +90,48 @@ def test_quantisation_aware_fit_follows_the_oracle(use_graph, skin):
     np.testing.assert_allclose(tr, ref, rtol=1e-3)
     _, plain = oracle_fit(xy, chol, rgb, frame, 1, lr=1e-2)
     assert abs(tr[0] - plain[0]) > 1e-4 * plain[0]   # the quantised point is not the plain one
+
+
+@pytest.mark.parametrize("N,bits", [(1, (6, 6)), (256, (3, 12)), (1024, (12, 12)), (1025, (1, 7)),
+                                    (66000, (6, 6))])
+def test_ptq_block_edges(N, bits):
+    print(f"ptq N={N} {bits}", flush=True)
+    xy, chol, rgb = _gaussians(N, N + 5)
+    ref = oracle_ptq(xy, chol, rgb, *bits)
+    got = _lib.ptq(dev(xy), dev(chol), dev(rgb), *bits, want_codes=True)
+    for k in ("xy", "chol", "rgb", "ranges"):
+        np.testing.assert_array_equal(host(got[k]), ref[k])
+    np.testing.assert_array_equal(host(got["codes"])[:, 2:], ref["codes"])
+    b = host(got["bits"])
+    np.testing.assert_allclose(b[:6], ref["component_bits"], rtol=1e-12, atol=1e-9)
+    assert abs(b[6] - ref["bits"]) <= 1e-12 * ref["bits"]
+
+
+@pytest.mark.parametrize("N", [255, 257, 1500])
+def test_quantisation_aware_routes_agree(N):
+    """400x344: 2150 tiles of 8 px (separate quantiser launches) and 550 of
+    16 (the quantiser inside the projection), and there the extremes taken
+    by the optimiser step (one chunk) or by their own launch (a chunk per
+    iteration); half of the Gaussians held.  The first loss and the ranges
+    are the same, the rest differs by the order of the gradients' atomics."""
+    print(f"qat routes N={N}", flush=True)
+    W, H = 400, 344
+    frame, _ = synth.make_frame(W, H, seed=101)
+    init = synth.random_gaussians(N, W, H, seed=102)
+    active = torch.from_numpy((np.arange(N) % 2).astype(np.uint8)).to(DEV)
+    out = []
+    for tile, chunk in ((8, 6), (16, 6), (16, 1)):
+        f = GpuFrame(W, H, N, tile)
+        P = [dev(a) for a in init]
+        M, V = torch.zeros(8 * N, device=DEV), torch.zeros(8 * N, device=DEV)
+        step = torch.zeros(1, dtype=torch.int32, device=DEV)
+        trace = torch.zeros(16, device=DEV)
+        _lib.fit_frame(f.shape, dev(frame), *P, M, V, step, trace, f.ws,
+                       _lib.fit_opts(6, chunk, cfg=_lib.adam_cfg(1e-2), qat=(5, 6), active=active))
+        held = host(active) == 0
+        for p, a in zip(P, init):
+            np.testing.assert_array_equal(host(p)[held], a[held])
+        out.append(host(trace)[:6])
+    for tr in out[1:]:
+        assert abs(tr[0] - out[0][0]) <= 1e-6 * out[0][0]
+        np.testing.assert_allclose(tr, out[0], rtol=1e-3)

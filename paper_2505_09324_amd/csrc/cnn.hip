@@ -858,14 +858,8 @@ k_cnn_adam(size_t n, CnnParamMap map, float *__restrict__ p, float *__restrict__
            float *__restrict__ m, float *__restrict__ v, const int32_t *__restrict__ step,
            float lr, float b1, float b2, float eps, float wd, uint16_t *__restrict__ wb,
            uint16_t *__restrict__ wt) {
-  __shared__ float s_bc1, s_bc2;
-  if (threadIdx.x == 0) {
-    const int t = step[0];
-    s_bc1 = (float)(1.0 - pow((double)b1, (double)t));
-    s_bc2 = (float)(1.0 - pow((double)b2, (double)t));
-  }
-  __syncthreads();
-  const float bc1 = s_bc1, bc2 = s_bc2;
+  float bc1, bc2;
+  adam_bias(step[0], b1, b2, &bc1, &bc2);
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
        i += (size_t)gridDim.x * blockDim.x) {
     const float gr = g[i], p0 = p[i];

@@ -81,10 +81,24 @@ __device__ inline float adam_update(float theta, float g, float *__restrict__ m,
   return theta - lr * (mm / bc1) / (sqrtf(vv / bc2) + eps);
 }
 
-// Bias corrections of step t, evaluated in FP64 and rounded once.
+// Bias corrections of step t, evaluated in FP64 and rounded once.  The
+// powers by squaring: their error, at most t 2^-53 b^t < 5e-14 for b <=
+// 0.999, is far below the rounding to FP32, and every thread forms them before
+// it can update anything (two calls of pow were 5 KB of code, fetched and run
+// in full by every launch: 1.9 us of the 6.6 us of a fitting iteration's
+// optimiser step at 1000 Gaussians).
 __device__ inline void adam_bias(int t, float b1, float b2, float *bc1, float *bc2) {
-  *bc1 = (float)(1.0 - pow((double)b1, (double)t));
-  *bc2 = (float)(1.0 - pow((double)b2, (double)t));
+  double x1 = b1, x2 = b2, p1 = 1.0, p2 = 1.0;
+  for (unsigned n = t < 0 ? 0u - (unsigned)t : (unsigned)t; n; n >>= 1) {
+    if (n & 1) {
+      p1 *= x1;
+      p2 *= x2;
+    }
+    x1 *= x1;
+    x2 *= x2;
+  }
+  *bc1 = (float)(1.0 - (t < 0 ? 1.0 / p1 : p1));
+  *bc2 = (float)(1.0 - (t < 0 ? 1.0 / p2 : p2));
 }
 
 // One thread's share of a block-wide FP64 sum of n floats (element i goes

@@ -314,8 +314,8 @@ template <int TILE, int PPL>
 __global__ void __launch_bounds__((Cfg<TILE, PPL>::NT)) GS2D_RASTER_OCCUPANCY
 k_b_render_persistent(BatchRaster a) {
   using C = Cfg<TILE, PPL>;
-  __shared__ Smem<C::NW> S;
-  __shared__ float acc[CH * 8];
+  __shared__ Smem<C> S;
+  __shared__ float acc[C::CH * 8];
   __shared__ unsigned s_item;
   for (;;) {
     if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1u);
@@ -339,21 +339,27 @@ k_b_render_persistent(BatchRaster a) {
     fa.sig_lo = fa.sig_hi = 0;
     fa.tick = nullptr;
     const float gs = (float)(2.0 / (3.0 * (double)d.W * (double)d.H));
-    fused_tile<TILE, PPL, false>(S, acc, fa, t, a.targets + d.px_off,
-                          a.loss_part + (d.tile_off + t) * Cfg<TILE, PPL>::NW, gs,
-                          a.g_xy + 2 * d.g_off, a.g_chol + 3 * d.g_off, a.g_rgb + 3 * d.g_off);
+    fused_tile<C, TILE, PPL, false>(S, acc, nullptr, fa, t, a.targets + d.px_off,
+                                    a.loss_part + (d.tile_off + t) * C::NWT, gs,
+                                    a.g_xy + 2 * d.g_off, a.g_chol + 3 * d.g_off,
+                                    a.g_rgb + 3 * d.g_off);
   }
 }
 
 // One workgroup per queue item (the queue's order is the dispatch order):
-// the one-frame kernel's single-tile path, exact block masks included.
-template <int TILE, int PPL>
-__global__ void __launch_bounds__((Cfg<TILE, PPL>::NT)) GS2D_RASTER_OCCUPANCY
+// the one-frame kernel's single-tile path, exact block masks included.  Every
+// sub-block keeps one wavefront, whatever the batch's size: the two launches
+// sum a pixel's terms in the same order.
+template <int TILE, int PPL, int SPLIT>
+__global__ void __launch_bounds__((Cfg<TILE, PPL, SPLIT>::NT)) GS2D_RASTER_OCCUPANCY
 k_b_render_grid(BatchRaster a) {
-  using C = Cfg<TILE, PPL>;
-  __shared__ Smem<C::NW> S;
-  __shared__ float acc[CH * 8];
-  const uint32_t q = a.queue[blockIdx.x];
+  using C = Cfg<TILE, PPL, SPLIT>;
+  __shared__ Smem<C> S;
+  __shared__ float acc[C::CH * 8];
+  int part;
+  const unsigned item = (unsigned)tile_of_block<SPLIT>(&part);
+  if (SPLIT > 1 && item >= a.n_items) return;
+  const uint32_t q = a.queue[item];
   const int f = (int)(q >> 16), t = (int)(q & 0xFFFFu);
   const BFrame d = a.D[f];
   FrameArgs fa;
@@ -369,10 +375,10 @@ k_b_render_grid(BatchRaster a) {
   fa.sig_lo = fa.sig_hi = 0;
   fa.tick = nullptr;
   const float gs = (float)(2.0 / (3.0 * (double)d.W * (double)d.H));
-  fused_tile<TILE, PPL, true, true>(S, acc, fa, t, a.targets + d.px_off,
-                                    a.loss_part + (d.tile_off + t) * C::NW, gs,
-                                    a.g_xy + 2 * d.g_off, a.g_chol + 3 * d.g_off,
-                                    a.g_rgb + 3 * d.g_off);
+  fused_tile<C, TILE, PPL, true, true>(S, acc, nullptr, fa, t, a.targets + d.px_off,
+                                       a.loss_part + (d.tile_off + t) * C::NWT, gs,
+                                       a.g_xy + 2 * d.g_off, a.g_chol + 3 * d.g_off,
+                                       a.g_rgb + 3 * d.g_off, part);
 }
 
 // One block per frame: loss of this iteration into trace[(t-1) * F + f].
@@ -458,9 +464,9 @@ int persistent_grid() {
 }
 
 int batch_grid(const BatchLayout &B) {
-#define CASE(TT, PP) \
+#define CASE(TT, PP, SP, SPS) \
   if (B.T == TT && B.ppl == PP) return persistent_grid<TT, PP>();
-  CASE(8, 1) CASE(16, 1) CASE(16, 2) CASE(32, 1) CASE(32, 2) CASE(32, 4)
+  GS2D_VARIANTS(CASE)
 #undef CASE
   return 0;
 }
@@ -526,17 +532,17 @@ hipError_t enqueue_batch_raster(const BatchLayout &B, void *ws, int grid, const 
   a.g_chol = g_chol;
   a.g_rgb = g_rgb;
   bool done = false;
-#define CASE(TT, PP)                                                                          \
-  if (!done && B.T == TT && B.ppl == PP) {                                                    \
+#define CASE(TT, PP, SP, SPS)                                                                \
+  if (!done && B.T == TT && B.ppl == PP) {                                                   \
     if (persistent)                                                                          \
-      hipLaunchKernelGGL((k_b_render_persistent<TT, PP>), dim3(grid), dim3(Cfg<TT, PP>::NT),   \
-                         0, st, a);                                                           \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_b_render_grid<TT, PP>), dim3(a.n_items), dim3(Cfg<TT, PP>::NT), 0, \
-                         st, a);                                                              \
-    done = true;                                                                              \
+      hipLaunchKernelGGL((k_b_render_persistent<TT, PP>), dim3(grid), dim3(Cfg<TT, PP>::NT), \
+                         0, st, a);                                                          \
+    else                                                                                     \
+      hipLaunchKernelGGL((k_b_render_grid<TT, PP, SP>), dim3(split_grid(a.n_items, SP)),     \
+                         dim3(Cfg<TT, PP, SP>::NT), 0, st, a);                               \
+    done = true;                                                                             \
   }
-  CASE(8, 1) CASE(16, 1) CASE(16, 2) CASE(32, 1) CASE(32, 2) CASE(32, 4)
+  GS2D_VARIANTS(CASE)
 #undef CASE
   return done ? hipGetLastError() : hipErrorInvalidValue;
 }

@@ -25,29 +25,36 @@
 namespace gs2d {
 
 // ----------------------------------------------------------------- forward --
-template <int TILE, int PPL>
-__global__ void __launch_bounds__((Cfg<TILE, PPL>::NT)) GS2D_RASTER_OCCUPANCY
+template <int TILE, int PPL, int SPLIT, int LS>
+__global__ void __launch_bounds__((Cfg<TILE, PPL, SPLIT, LS>::NT)) GS2D_RASTER_OCCUPANCY
 k_render_fwd(FrameArgs f, const float *__restrict__ target, float *__restrict__ img,
-             float *__restrict__ dl_dimg, float *__restrict__ loss_part, float grad_scale) {
-  using C = Cfg<TILE, PPL>;
-  __shared__ Smem<C::NW> S;
-  const int tile = blockIdx.x;
+             float *__restrict__ dl_dimg, float *__restrict__ loss_part, float grad_scale,
+             int n_tiles) {
+  using C = Cfg<TILE, PPL, SPLIT, LS>;
+  __shared__ Smem<C> S;
+  __shared__ float xch[C::XCH];
+  int part;
+  const int tile = tile_of_block<SPLIT>(&part);
+  if (SPLIT > 1 && tile >= n_tiles) return;
   const int tx = tile % f.TX, ty = tile / f.TX;
   const int beg = f.tile_start[tile], end = f.tile_start[tile + 1];
   int px, py0;
-  pixel_of_thread<TILE, PPL>(tx, ty, &px, &py0);
+  pixel_of_thread<C, TILE, PPL>(tx, ty, &px, &py0, part);
   const float pxc = (float)px + 0.5f, pyc0 = (float)py0 + 0.5f;
   const unsigned inside = inside_mask<PPL>(f, px, py0);
   float acc[PPL][3] = {};
-  for (int c = beg; c < end; c += CH) {
-    const int cnt = min(CH, end - c);
+  for (int c = beg; c < end; c += C::CH) {
+    const int cnt = min(C::CH, end - c);
+    if (c != beg) __syncthreads();
+    stage_chunk<C, TILE>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, nullptr, part);
     __syncthreads();
-    stage_chunk<TILE, PPL>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb);
-    __syncthreads();
-    const int len = compact_chunk<C::NW>(S, cnt);
-    __syncthreads();
-    fwd_chunk<C::NW, PPL, false>(S, len, pxc, pyc0, inside, acc);
+    int kb, ke;
+    list_run<C>(compact_chunk<C>(S, cnt), &kb, &ke);
+    fwd_chunk<C, PPL, false>(S, kb, ke, pxc, pyc0, inside, acc);
   }
+  exchange_sums<C, PPL>(xch, acc);
+  const int w = threadIdx.x >> 6;
+  if (w >= C::NB) return;  // the first wavefront of a sub-block writes it
   float l = 0.f;
   const size_t HW = (size_t)f.W * f.H;
 #pragma unroll
@@ -70,23 +77,25 @@ k_render_fwd(FrameArgs f, const float *__restrict__ target, float *__restrict__ 
       }
     }
   }
-  if (loss_part) wave_loss(l, loss_part + tile * C::NW + (threadIdx.x >> 6));
+  if (loss_part) wave_loss(l, loss_part + tile * C::NWT + part * C::NB + w);
 }
 
 // ---------------------------------------------------------------- backward --
-template <int TILE, int PPL>
-__global__ void __launch_bounds__((Cfg<TILE, PPL>::NT)) GS2D_RASTER_OCCUPANCY
+template <int TILE, int PPL, int SPLIT, int LS>
+__global__ void __launch_bounds__((Cfg<TILE, PPL, SPLIT, LS>::NT)) GS2D_RASTER_OCCUPANCY
 k_render_bwd(FrameArgs f, const float *__restrict__ dl_dimg, float *__restrict__ g_xy,
-             float *__restrict__ g_chol, float *__restrict__ g_rgb) {
-  using C = Cfg<TILE, PPL>;
-  __shared__ Smem<C::NW> S;
-  __shared__ float acc[CH * 8];
-  const int tile = blockIdx.x;
+             float *__restrict__ g_chol, float *__restrict__ g_rgb, int n_tiles) {
+  using C = Cfg<TILE, PPL, SPLIT, LS>;
+  __shared__ Smem<C> S;
+  __shared__ float acc[C::CH * 8];
+  int part;
+  const int tile = tile_of_block<SPLIT>(&part);
+  if (SPLIT > 1 && tile >= n_tiles) return;
   const int tx = tile % f.TX, ty = tile / f.TX;
   const int beg = f.tile_start[tile], end = f.tile_start[tile + 1];
   if (beg >= end) return;
   int px, py0;
-  pixel_of_thread<TILE, PPL>(tx, ty, &px, &py0);
+  pixel_of_thread<C, TILE, PPL>(tx, ty, &px, &py0, part);
   const float pxc = (float)px + 0.5f, pyc0 = (float)py0 + 0.5f;
   const unsigned inside = inside_mask<PPL>(f, px, py0);
   float g[PPL][3];
@@ -101,29 +110,30 @@ k_render_bwd(FrameArgs f, const float *__restrict__ dl_dimg, float *__restrict__
       g[r][2] = dl_dimg[2 * HW + p];
     }
   }
-  for (int c = beg; c < end; c += CH) {
-    const int cnt = min(CH, end - c);
+  for (int c = beg; c < end; c += C::CH) {
+    const int cnt = min(C::CH, end - c);
+    if (c != beg) __syncthreads();
+    stage_chunk<C, TILE>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, nullptr, part);
+    for (int i = threadIdx.x; i < cnt * 8; i += C::NT) acc[i] = 0.f;
     __syncthreads();
-    stage_chunk<TILE, PPL>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb);
-    for (int i = threadIdx.x; i < CH * 8; i += C::NT) acc[i] = 0.f;
+    int kb, ke;
+    list_run<C>(compact_chunk<C>(S, cnt), &kb, &ke);
+    bwd_chunk<C, PPL, false>(S, acc, kb, ke, pxc, pyc0, g);
     __syncthreads();
-    const int len = compact_chunk<C::NW>(S, cnt);
-    __syncthreads();
-    bwd_chunk<C::NW, PPL, false>(S, acc, len, pxc, pyc0, g);
-    __syncthreads();
-    flush_grads<C::NT, C::NW>(S, acc, cnt, g_xy, g_chol, g_rgb);
+    flush_grads<C, true>(S, acc, cnt, g_xy, g_chol, g_rgb);
   }
 }
 
 // ------------------------------------------- fused forward + loss + backward --
-template <int TILE, int PPL>
-__global__ void __launch_bounds__((Cfg<TILE, PPL>::NT)) GS2D_RASTER_OCCUPANCY
+template <int TILE, int PPL, int SPLIT, int LS>
+__global__ void __launch_bounds__((Cfg<TILE, PPL, SPLIT, LS>::NT)) GS2D_RASTER_OCCUPANCY
 k_render_fused(FrameArgs f, const float *__restrict__ target, float *__restrict__ loss_part,
                float grad_scale, float *__restrict__ g_xy, float *__restrict__ g_chol,
-               float *__restrict__ g_rgb) {
-  using C = Cfg<TILE, PPL>;
-  __shared__ Smem<C::NW> S;
-  __shared__ float acc[CH * 8];
+               float *__restrict__ g_rgb, int n_tiles) {
+  using C = Cfg<TILE, PPL, SPLIT, LS>;
+  __shared__ Smem<C> S;
+  __shared__ float acc[C::CH * 8];
+  __shared__ float xch[C::XCH];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (f.lazy_misc && f.lazy_misc[MISC_STALE]) {
       const bool ok = !(f.lazy_misc[MISC_STICKY] & (int)STATUS_STALLED);
@@ -133,9 +143,11 @@ k_render_fused(FrameArgs f, const float *__restrict__ target, float *__restrict_
     }
     if (f.tick) *f.tick += 1;
   }
-  fused_tile<TILE, PPL, true, true>(S, acc, f, (int)blockIdx.x, target,
-                                    loss_part + blockIdx.x * C::NW, grad_scale, g_xy, g_chol,
-                                    g_rgb);
+  int part;
+  const int tile = tile_of_block<SPLIT>(&part);
+  if (SPLIT > 1 && tile >= n_tiles) return;
+  fused_tile<C, TILE, PPL, true, true>(S, acc, xch, f, tile, target, loss_part + tile * C::NWT,
+                                       grad_scale, g_xy, g_chol, g_rgb, part);
 }
 
 // ------------------------------------------------- in-cutoff pair counting --
@@ -145,22 +157,22 @@ template <int TILE>
 __global__ void __launch_bounds__((Cfg<TILE, 1>::NT))
 k_count_pairs(FrameArgs f, unsigned long long *__restrict__ out) {
   using C = Cfg<TILE, 1>;
-  __shared__ Smem<C::NW> S;
+  __shared__ Smem<C> S;
   const int tile = blockIdx.x;
   const int tx = tile % f.TX, ty = tile / f.TX;
   const int beg = f.tile_start[tile], end = f.tile_start[tile + 1];
   int px, py;
-  pixel_of_thread<TILE, 1>(tx, ty, &px, &py);
+  pixel_of_thread<C, TILE, 1>(tx, ty, &px, &py);
   const float pxc = (float)px + 0.5f, pyc = (float)py + 0.5f;
   const bool inside = px < f.W && py < f.H;
   const int w = threadIdx.x >> 6;
   unsigned int n = 0;
-  for (int c = beg; c < end; c += CH) {
-    const int cnt = min(CH, end - c);
+  for (int c = beg; c < end; c += C::CH) {
+    const int cnt = min(C::CH, end - c);
     __syncthreads();
-    stage_chunk<TILE, 1>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, nullptr);
+    stage_chunk<C, TILE>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, nullptr);
     __syncthreads();
-    const int len = compact_chunk<C::NW>(S, cnt);
+    const int len = compact_chunk<C>(S, cnt);
     __syncthreads();
     for (int k = 0; k < len; ++k) {
       const int j = S.list[w][k];
@@ -209,20 +221,26 @@ static FrameArgs frame_args(const Layout &L, void *ws, const float *rgb) {
 
 static float grad_scale(const Layout &L) { return (float)(2.0 / (3.0 * L.W * (double)L.H)); }
 
-// (tile, pixels per lane) variants that are compiled.
-#define GS2D_VARIANTS(X) X(8, 1) X(16, 1) X(16, 2) X(32, 1) X(32, 2) X(32, 4)
+// KERNEL<TT, PP, SPLIT, LS> for the layout's variant.
+#define GS2D_LAUNCH_LS(KERNEL, TT, PP, SP, LS, ...)                             \
+  hipLaunchKernelGGL((KERNEL<TT, PP, SP, LS>), dim3(split_grid(L.n_tiles, SP)), \
+                     dim3(Cfg<TT, PP, SP, LS>::NT), 0, st, __VA_ARGS__, L.n_tiles)
+#define GS2D_LAUNCH(KERNEL, TT, PP, SP, SPS, ...)                        \
+  if (!done && L.T == TT && L.ppl == PP) {                               \
+    const int share = raster_share(L.loss_parts);                        \
+    if (share == 4) GS2D_LAUNCH_LS(KERNEL, TT, PP, SPS, 4, __VA_ARGS__); \
+    else if (share == 2) GS2D_LAUNCH_LS(KERNEL, TT, PP, SPS, 2, __VA_ARGS__); \
+    else GS2D_LAUNCH_LS(KERNEL, TT, PP, SP, 1, __VA_ARGS__);             \
+    done = true;                                                         \
+  }
 
 hipError_t launch_render_fwd(const Layout &L, void *ws, const float *rgb, const float *target,
                              float *img, float *dl_dimg, hipStream_t st) {
   FrameArgs f = frame_args(L, ws, rgb);
   float *lp = target ? at<float>(ws, L.loss_part) : nullptr;
   bool done = false;
-#define CALL(TT, PP)                                                                       \
-  if (!done && L.T == TT && L.ppl == PP) {                                                 \
-    hipLaunchKernelGGL((k_render_fwd<TT, PP>), dim3(L.n_tiles), dim3(Cfg<TT, PP>::NT), 0, st, \
-                       f, target, img, dl_dimg, lp, grad_scale(L));                        \
-    done = true;                                                                           \
-  }
+#define CALL(TT, PP, SP, SPS) \
+  GS2D_LAUNCH(k_render_fwd, TT, PP, SP, SPS, f, target, img, dl_dimg, lp, grad_scale(L))
   GS2D_VARIANTS(CALL)
 #undef CALL
   return done ? hipGetLastError() : hipErrorInvalidValue;
@@ -232,12 +250,8 @@ hipError_t launch_render_bwd(const Layout &L, void *ws, const float *rgb, const 
                              float *g_xy, float *g_chol, float *g_rgb, hipStream_t st) {
   FrameArgs f = frame_args(L, ws, rgb);
   bool done = false;
-#define CALL(TT, PP)                                                                       \
-  if (!done && L.T == TT && L.ppl == PP) {                                                 \
-    hipLaunchKernelGGL((k_render_bwd<TT, PP>), dim3(L.n_tiles), dim3(Cfg<TT, PP>::NT), 0, st, \
-                       f, dl_dimg, g_xy, g_chol, g_rgb);                                   \
-    done = true;                                                                           \
-  }
+#define CALL(TT, PP, SP, SPS) \
+  GS2D_LAUNCH(k_render_bwd, TT, PP, SP, SPS, f, dl_dimg, g_xy, g_chol, g_rgb)
   GS2D_VARIANTS(CALL)
 #undef CALL
   return done ? hipGetLastError() : hipErrorInvalidValue;
@@ -256,12 +270,9 @@ hipError_t launch_render_fused(const Layout &L, void *ws, const float *rgb, cons
   f.tick = tick;
   float *lp = at<float>(ws, L.loss_part);
   bool done = false;
-#define CALL(TT, PP)                                                                           \
-  if (!done && L.T == TT && L.ppl == PP) {                                                     \
-    hipLaunchKernelGGL((k_render_fused<TT, PP>), dim3(L.n_tiles), dim3(Cfg<TT, PP>::NT), 0, st, \
-                       f, target, lp, grad_scale(L), g_xy, g_chol, g_rgb);                     \
-    done = true;                                                                               \
-  }
+#define CALL(TT, PP, SP, SPS)                                                        \
+  GS2D_LAUNCH(k_render_fused, TT, PP, SP, SPS, f, target, lp, grad_scale(L), g_xy, g_chol, \
+              g_rgb)
   GS2D_VARIANTS(CALL)
 #undef CALL
   return done ? hipGetLastError() : hipErrorInvalidValue;

@@ -16,33 +16,96 @@ constexpr float EXP_SCALE = 0.84932180028801904f;     // sqrt(log2(e)/2)
 constexpr float CUTOFF_QS = 6.4921276840003355f;      // 9 log2(e)/2
 constexpr float INV_H = 1.3862943611198906f;          // 2 / log2(e)
 constexpr float INV_H15 = 1.6322368749392462f;        // (2 / log2(e))^1.5
-constexpr int CH = 256;  // Gaussians staged per LDS chunk
 
-// Raster kernels are compiled for 8 wavefronts per SIMD (at most 64 VGPRs
-// where the LDS allows it): with 512-thread tiles that is 4 workgroups per
-// CU, the wave-slot limit, which the latency of staging and the barriers
-// between a tile's phases need.
+// Raster kernels are compiled for 8 wavefronts per SIMD (at most 64 VGPRs):
+// with 256-thread workgroups that is 8 workgroups per CU, the wave-slot limit,
+// which the latency of staging and the barriers between a tile's phases need.
 #define GS2D_RASTER_OCCUPANCY __attribute__((amdgpu_waves_per_eu(8, 8)))
 
-template <int TILE, int PPL>
+// SPLIT workgroups share a tile, each taking NB consecutive sub-blocks of it
+// (whole rows of sub-blocks, or part of one row); LS wavefronts share a
+// sub-block, each taking one of LS runs of its Gaussian list and exchanging
+// the forward sums through LDS.  Wavefront w: sub-block w % NB, run w / NB.
+template <int TILE, int PPL, int SPLIT = 1, int LS = 1>
 struct Cfg {
   static constexpr int SBH = 8 * PPL;      // sub-block height (px)
   static constexpr int SBX = TILE / 8;     // sub-blocks per tile row
   static constexpr int SBY = TILE / SBH;   // sub-block rows per tile
-  static constexpr int NW = SBX * SBY;     // wavefronts per tile
-  static constexpr int NT = NW * 64;       // threads per tile
-  static_assert(SBY >= 1 && NW <= 16, "unsupported tile / pixels-per-lane");
+  static constexpr int NWT = SBX * SBY;    // sub-blocks per tile
+  static constexpr int NB = NWT / SPLIT;   // sub-blocks per workgroup
+  static constexpr int NW = NB * LS;       // wavefronts per workgroup
+  static constexpr int NT = NW * 64;       // threads per workgroup
+  // Gaussians staged per LDS chunk: fewer where a workgroup has only one or
+  // two sub-blocks, so that the LDS of 32 wavefronts' workgroups fits one
+  // compute unit (256 everywhere left 8 x 8 tiles 2 and 16 x 16 tiles with 2
+  // pixels per lane 4 of 8 wavefronts per SIMD).
+  static constexpr int CH = NWT == 1 ? 64 : NWT == 2 ? 128 : 256;
+  // floats the wavefronts of a sub-block exchange
+  static constexpr int XCH = LS > 1 ? NW * 64 * PPL * 3 : 1;
+  static_assert(SBY >= 1 && NWT <= 16, "unsupported tile / pixels-per-lane");
+  static_assert(NB * SPLIT == NWT && (NB % SBX == 0 || SBX % NB == 0), "unsupported split");
+  static_assert(NT <= 1024, "workgroup too large");
 };
 
-template <int NW>
+// (tile, pixels per lane) variants that are compiled, with SPLIT where the
+// frame's sub-blocks fill the device and where they do not (LS > 1).
+//
+// SPLIT: a workgroup of 4 wavefronts.  A tile's workgroup lives until its
+// slowest wavefront is done, so smaller ones leave a shorter tail at the end
+// of a launch and fewer idle wavefronts before each barrier, at the price of
+// staging the tile's list once per part.  Fits of 20 iterations at 1920x1080 /
+// 30,000, us: 32/2 (8 sub-blocks) whole 1345, halves 1300, quarters 1431;
+// 32/1 (16) whole 1645, halves 1453, quarters 1364; 32/4 and the 16-pixel
+// tiles (4 and 2) do not gain.
+#define GS2D_VARIANTS(X) \
+  X(8, 1, 1, 1) X(16, 1, 1, 1) X(16, 2, 1, 1) X(32, 1, 4, 4) X(32, 2, 2, 4) X(32, 4, 1, 2)
+
+// LS: the device holds 8192 wavefronts.  A frame with at most a quarter as
+// many sub-blocks is bound by the serial pass over each one's list, so four
+// wavefronts share it; up to a half, two.  us per iteration at 480x270 / 1200
+// (32/2: 1080 sub-blocks) 27.5 -> 20.8, 640x360 / 1000 (1920) 24.6 -> 20.5 and
+// at 960x540 / 7000 (4080) 34.6 -> 31.7; at 1280x720 (7360) two are no faster,
+// and at 16/1 four at 3680 sub-blocks are slower than one (24.5 against 23.7).
+inline int raster_share(long long sub_blocks) {
+  return sub_blocks <= 2048 ? 4 : sub_blocks <= 4096 ? 2 : 1;
+}
+
+// The workgroup's tile (or work item) and its part of it: the parts run on one
+// XCD (workgroup b runs on XCD b % 8).  A grid of split_grid workgroups covers
+// every part; those past the last tile leave at once.
+template <int SPLIT>
+__device__ inline int tile_of_block(int *part) {
+  const int b = (int)blockIdx.x;
+  *part = SPLIT == 1 ? 0 : (b >> 3) % SPLIT;
+  return SPLIT == 1 ? b : b / (8 * SPLIT) * 8 + (b & 7);
+}
+inline unsigned split_grid(unsigned n_tiles, unsigned split) {
+  return split == 1 ? n_tiles : (n_tiles + 7) / 8 * 8 * split;
+}
+
+template <class C>
 struct Smem {
-  float4 A[CH];           // mx, my, 1/l1, l2
-  float4 B[CH];           // 1/l3, c'0, c'1, c'2
-  uint16_t mask[CH];      // bit w: box meets sub-block w (at most 16)
-  int id[CH];
-  uint16_t list[NW][CH];
-  uint8_t act[CH];        // the Gaussian is optimised (FrameArgs::active)
+  float4 A[C::CH];           // mx, my, 1/l1, l2
+  float4 B[C::CH];           // 1/l3, c'0, c'1, c'2
+  uint16_t mask[C::CH];      // bit w: box meets sub-block w (at most 16)
+  int id[C::CH];
+  uint16_t list[C::NW][C::CH];
+  uint8_t act[C::CH];        // the Gaussian is optimised (FrameArgs::active)
 };
+
+// This wavefront's run [beg, end) of a list of len entries.
+template <class C>
+__device__ inline void list_run(int len, int *beg, int *end) {
+  if constexpr (C::NW == C::NB) {
+    *beg = 0;
+    *end = len;
+  } else {
+    constexpr int LS = C::NW / C::NB;
+    const int r = (int)(threadIdx.x >> 6) / C::NB;
+    *beg = len * r / LS;
+    *end = len * (r + 1) / LS;
+  }
+}
 
 struct FrameArgs {
   int W, H, TX;
@@ -107,12 +170,15 @@ __device__ inline bool ellipse_meets_rect(float mx, float my, float a, float l2s
 // leave few Gaussians without a pixel in the cutoff, so their users skip
 // the per-Gaussian hit checks; the persistent batched kernel, whose
 // register budget the test's live values overrun, keeps box masks.
-template <int TILE, int PPL, bool EXACT = true>
-__device__ inline void stage_chunk(Smem<Cfg<TILE, PPL>::NW> &S, const uint32_t *__restrict__ keys,
-                                   int beg, int cnt, int tx, int ty, int W, int H,
-                                   const float4 *__restrict__ geom, const float *__restrict__ rgb,
-                                   const uint8_t *__restrict__ active = nullptr) {
-  using C = Cfg<TILE, PPL>;
+template <class C, int TILE, bool EXACT = true>
+__device__ inline void stage_chunk(Smem<C> &S, const uint32_t *__restrict__ keys, int beg, int cnt,
+                                   int tx, int ty, int W, int H, const float4 *__restrict__ geom,
+                                   const float *__restrict__ rgb,
+                                   const uint8_t *__restrict__ active = nullptr, int part = 0) {
+  // the workgroup's sub-blocks: rows [sy0, sy1], columns [sx0, sx1] of the tile's
+  constexpr int ROWS = C::NB >= C::SBX ? C::NB / C::SBX : 1;
+  const int sb0 = part * C::NB, sy0 = sb0 / C::SBX, sy1 = sy0 + ROWS - 1;
+  const int sx0 = sb0 % C::SBX, sx1 = C::NB >= C::SBX ? C::SBX - 1 : sx0 + C::NB - 1;
   constexpr float inv_w = 0.125f, inv_h = 1.0f / (float)C::SBH;
   const float xlast = (float)W - 0.5f, ylast = (float)H - 0.5f;  // last pixel centres
   for (int j = threadIdx.x; j < cnt; j += C::NT) {
@@ -136,8 +202,8 @@ __device__ inline void stage_chunk(Smem<Cfg<TILE, PPL>::NW> &S, const uint32_t *
     const float bx1f = floorf(xhi * inv_w) - (float)(tx * C::SBX);
     const float by0f = floorf(ylo * inv_h) - (float)(ty * C::SBY);
     const float by1f = floorf(yhi * inv_h) - (float)(ty * C::SBY);
-    const int bx0 = (int)fmaxf(bx0f, 0.f), bx1 = (int)fminf(bx1f, (float)(C::SBX - 1));
-    const int by0 = (int)fmaxf(by0f, 0.f), by1 = (int)fminf(by1f, (float)(C::SBY - 1));
+    const int bx0 = (int)fmaxf(bx0f, (float)sx0), bx1 = (int)fminf(bx1f, (float)sx1);
+    const int by0 = (int)fmaxf(by0f, (float)sy0), by1 = (int)fminf(by1f, (float)sy1);
     const float qmax = CUTOFF_QS + 0.01f * (1.0f + fabsf(l2s * r3s));
     uint32_t m = 0;
     for (int by = by0; by <= by1; ++by) {
@@ -148,7 +214,7 @@ __device__ inline void stage_chunk(Smem<Cfg<TILE, PPL>::NW> &S, const uint32_t *
         const float X1 = fminf(X0 + 7.0f, xlast);
         if (!EXACT ||
             (X0 <= X1 && Y0 <= Y1 && ellipse_meets_rect(g0.x, g0.y, a, l2s, r3s, X0, X1, Y0, Y1, qmax)))
-          m |= 1u << (by * C::SBX + bx);
+          m |= 1u << (by * C::SBX + bx - sb0);
       }
     }
     S.mask[j] = (uint16_t)m;
@@ -156,14 +222,14 @@ __device__ inline void stage_chunk(Smem<Cfg<TILE, PPL>::NW> &S, const uint32_t *
 }
 
 // Each wavefront builds its list of staged Gaussians; returns its length.
-template <int NW>
-__device__ inline int compact_chunk(Smem<NW> &S, int cnt) {
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+template <class C>
+__device__ inline int compact_chunk(Smem<C> &S, int cnt) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, sb = w % C::NB;
   const unsigned long long lt = lanemask_lt();
   int len = 0;
   for (int j0 = 0; j0 < cnt; j0 += 64) {
     const int j = j0 + lane;
-    const bool hit = (j < cnt) && ((S.mask[j] >> w) & 1u);
+    const bool hit = (j < cnt) && ((S.mask[j] >> sb) & 1u);
     const unsigned long long bal = __ballot(hit);
     if (hit) S.list[w][len + __popcll(bal & lt)] = (uint16_t)j;
     len += __popcll(bal);
@@ -216,8 +282,8 @@ __device__ inline float reduce8_transpose(const float (&a)[8]) {
 
 // Drop the Gaussians whose staged active flag is 0 from this wavefront's
 // list (in place, order kept); returns the new length.
-template <int NW>
-__device__ inline int keep_active(Smem<NW> &S, int len) {
+template <class C>
+__device__ inline int keep_active(Smem<C> &S, int len) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const unsigned long long lt = lanemask_lt();
   int kept = 0;
@@ -232,24 +298,24 @@ __device__ inline int keep_active(Smem<NW> &S, int len) {
 }
 
 // Pixel column and first row of this thread.
-template <int TILE, int PPL>
-__device__ inline void pixel_of_thread(int tx, int ty, int *px, int *py0) {
-  using C = Cfg<TILE, PPL>;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+template <class C, int TILE, int PPL>
+__device__ inline void pixel_of_thread(int tx, int ty, int *px, int *py0, int part = 0) {
+  const int w = part * C::NB + (int)(threadIdx.x >> 6) % C::NB, lane = threadIdx.x & 63;
   *px = tx * TILE + (w % C::SBX) * 8 + (lane & 7);
   *py0 = ty * TILE + (w / C::SBX) * C::SBH + (lane >> 3) * PPL;
 }
 
-// Forward accumulation over one staged, compacted chunk.  With KEEP_HITS the
+// Forward accumulation over entries [beg, end) of this wavefront's list of a
+// staged, compacted chunk.  With KEEP_HITS (the whole list: beg = 0) the
 // wavefront's list is compacted in place to the Gaussians that have at least
 // one in-frame pixel with q <= 9 in this sub-block (the only ones the
-// backward pass needs); returns the new length (else `len`).
-template <int NW, int PPL, bool KEEP_HITS>
-__device__ inline int fwd_chunk(Smem<NW> &S, int len, float pxc, float pyc0, unsigned inside,
-                                float (&acc)[PPL][3]) {
+// backward pass needs); returns the new length (else `end`).
+template <class C, int PPL, bool KEEP_HITS>
+__device__ inline int fwd_chunk(Smem<C> &S, int beg, int end, float pxc, float pyc0,
+                                unsigned inside, float (&acc)[PPL][3]) {
   const int w = threadIdx.x >> 6;
   int kept = 0;
-  for (int k = 0; k < len; ++k) {
+  for (int k = beg; k < end; ++k) {
     const int j = S.list[w][k];
     const float4 A = S.A[j], B = S.B[j];
     const float u1 = (pxc - A.x) * A.z;
@@ -275,17 +341,38 @@ __device__ inline int fwd_chunk(Smem<NW> &S, int len, float pxc, float pyc0, uns
       }
     }
   }
-  return KEEP_HITS ? kept : len;
+  return KEEP_HITS ? kept : end;
 }
 
-// Backward over one staged, compacted chunk; adds into acc[CH][8] in LDS.
+// The sums of the LS wavefronts that share a sub-block, added in the order of
+// their runs: every one of them then holds the sub-block's pixels.
+template <class C, int PPL>
+__device__ inline void exchange_sums(float *xch, float (&acc)[PPL][3]) {
+  if constexpr (C::NW > C::NB) {
+    constexpr int LS = C::NW / C::NB, V = PPL * 3;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < V; ++i) xch[(w * V + i) * 64 + lane] = acc[i / 3][i % 3];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      float s = 0.f;
+#pragma unroll
+      for (int r = 0; r < LS; ++r) s += xch[((r * C::NB + w % C::NB) * V + i) * 64 + lane];
+      acc[i / 3][i % 3] = s;
+    }
+  }
+}
+
+// Backward over entries [beg, end) of this wavefront's list of a staged,
+// compacted chunk; adds into acc[CH][8] in LDS.
 // CHECK_HITS skips (uniformly per wavefront) Gaussians with no pixel inside
 // the cutoff, for lists that were not already reduced to such Gaussians.
-template <int NW, int PPL, bool CHECK_HITS>
-__device__ inline void bwd_chunk(const Smem<NW> &S, float *acc, int len, float pxc, float pyc0,
-                                 const float (&g)[PPL][3]) {
+template <class C, int PPL, bool CHECK_HITS>
+__device__ inline void bwd_chunk(const Smem<C> &S, float *acc, int beg, int end, float pxc,
+                                 float pyc0, const float (&g)[PPL][3]) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int k = 0; k < len; ++k) {
+  for (int k = beg; k < end; ++k) {
     const int j = S.list[w][k];
     const float4 A = S.A[j], B = S.B[j];
     const float u1 = (pxc - A.x) * A.z;
@@ -335,11 +422,11 @@ __device__ inline void bwd_chunk(const Smem<NW> &S, float *acc, int len, float p
 // compiler hoist them out of a caller's chunk loop, where they would hold
 // registers through the passes (which of the two spills less depends on the
 // caller).
-template <int NT, int NW, bool PIN = false>
-__device__ inline void flush_grads(const Smem<NW> &S, const float *acc, int cnt,
+template <class C, bool PIN = false>
+__device__ inline void flush_grads(const Smem<C> &S, const float *acc, int cnt,
                                    float *__restrict__ g_xy, float *__restrict__ g_chol,
                                    float *__restrict__ g_rgb) {
-  static_assert(NT % 8 == 0, "a thread keeps one parameter");
+  static_assert(C::NT % 8 == 0, "a thread keeps one parameter");
   int k = threadIdx.x & 7;
   if constexpr (PIN) asm volatile("" : "+v"(k));
   float *base;
@@ -358,7 +445,7 @@ __device__ inline void flush_grads(const Smem<NW> &S, const float *acc, int cnt,
     stride = 3;
     scale = 1.f;
   }
-  for (int e = threadIdx.x; e < cnt * 8; e += NT) {
+  for (int e = threadIdx.x; e < cnt * 8; e += C::NT) {
     const float v = acc[e];
     if (v != 0.f) atomicAdd(base + stride * S.id[e >> 3], v * scale);
   }
@@ -416,19 +503,19 @@ __device__ inline void residuals(const float (&a)[PPL][3], const float (&tg)[PPL
 }
 
 // ONE: the caller runs one tile per workgroup (no LDS of an earlier tile to
-// wait for before staging).
-template <int TILE, int PPL, bool EXACT = true, bool ONE = false>
-__device__ inline void fused_tile(Smem<Cfg<TILE, PPL>::NW> &S, float *acc, const FrameArgs &f,
-                                  int tile, const float *__restrict__ target,
+// wait for before staging).  loss_slots: the tile's, one per sub-block.
+template <class C, int TILE, int PPL, bool EXACT = true, bool ONE = false>
+__device__ inline void fused_tile(Smem<C> &S, float *acc, float *xch, const FrameArgs &f, int tile,
+                                  const float *__restrict__ target,
                                   float *__restrict__ loss_slots, float grad_scale,
                                   float *__restrict__ g_xy, float *__restrict__ g_chol,
-                                  float *__restrict__ g_rgb) {
-  using C = Cfg<TILE, PPL>;
+                                  float *__restrict__ g_rgb, int part = 0) {
+  static_assert(EXACT || C::NW == C::NB, "shared sub-blocks need exact masks");
   const int w = threadIdx.x >> 6;
   const int tx = tile % f.TX, ty = tile / f.TX;
   const int beg = f.tile_start[tile], end = f.tile_start[tile + 1];
   int px, py0;
-  pixel_of_thread<TILE, PPL>(tx, ty, &px, &py0);
+  pixel_of_thread<C, TILE, PPL>(tx, ty, &px, &py0, part);
   const float pxc = (float)px + 0.5f, pyc0 = (float)py0 + 0.5f;
   const unsigned inside = inside_mask<PPL>(f, px, py0);
   // the target pixels are loaded first, their latency hidden by the staging
@@ -444,43 +531,51 @@ __device__ inline void fused_tile(Smem<Cfg<TILE, PPL>::NW> &S, float *acc, const
   float a[PPL][3] = {};
   float g[PPL][3];
   float l;
-  if (end - beg <= CH) {
+  int kb, ke;
+  if (end - beg <= C::CH) {
     const int cnt = end - beg;
     if constexpr (!ONE) __syncthreads();  // LDS of a previous tile (persistent callers) is free
-    stage_chunk<TILE, PPL, EXACT>(S, f.keys, beg, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active);
+    stage_chunk<C, TILE, EXACT>(S, f.keys, beg, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active,
+                                part);
     for (int i = threadIdx.x; i < cnt * 8; i += C::NT) acc[i] = 0.f;
     __syncthreads();
-    int len = compact_chunk<C::NW>(S, cnt);
-    len = fwd_chunk<C::NW, PPL, !EXACT>(S, len, pxc, pyc0, inside, a);
+    int len = compact_chunk<C>(S, cnt);
+    list_run<C>(len, &kb, &ke);
+    const int kept = fwd_chunk<C, PPL, !EXACT>(S, kb, ke, pxc, pyc0, inside, a);
+    if constexpr (!EXACT) len = kept;
+    exchange_sums<C, PPL>(xch, a);
     residuals<TILE, PPL>(a, tg, inside, grad_scale, g, &l);
-    wave_loss(l, loss_slots + w);
-    if (f.active) len = keep_active<C::NW>(S, len);
-    bwd_chunk<C::NW, PPL, false>(S, acc, len, pxc, pyc0, g);
+    if (w < C::NB) wave_loss(l, loss_slots + part * C::NB + w);
+    if (f.active) len = keep_active<C>(S, len);
+    list_run<C>(len, &kb, &ke);
+    bwd_chunk<C, PPL, false>(S, acc, kb, ke, pxc, pyc0, g);
     __syncthreads();
-    flush_grads<C::NT, C::NW, ONE>(S, acc, cnt, g_xy, g_chol, g_rgb);
+    flush_grads<C, ONE>(S, acc, cnt, g_xy, g_chol, g_rgb);
     return;
   }
-  for (int c = beg; c < end; c += CH) {
-    const int cnt = min(CH, end - c);
+  for (int c = beg; c < end; c += C::CH) {
+    const int cnt = min(C::CH, end - c);
     __syncthreads();
-    stage_chunk<TILE, PPL, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb);
+    stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, nullptr, part);
     __syncthreads();
-    const int len = compact_chunk<C::NW>(S, cnt);
-    fwd_chunk<C::NW, PPL, false>(S, len, pxc, pyc0, inside, a);
+    list_run<C>(compact_chunk<C>(S, cnt), &kb, &ke);
+    fwd_chunk<C, PPL, false>(S, kb, ke, pxc, pyc0, inside, a);
   }
+  exchange_sums<C, PPL>(xch, a);
   residuals<TILE, PPL>(a, tg, inside, grad_scale, g, &l);
-  wave_loss(l, loss_slots + w);
-  for (int c = beg; c < end; c += CH) {
-    const int cnt = min(CH, end - c);
+  if (w < C::NB) wave_loss(l, loss_slots + part * C::NB + w);
+  for (int c = beg; c < end; c += C::CH) {
+    const int cnt = min(C::CH, end - c);
     __syncthreads();
-    stage_chunk<TILE, PPL, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active);
+    stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active, part);
     for (int i = threadIdx.x; i < cnt * 8; i += C::NT) acc[i] = 0.f;
     __syncthreads();
-    int len = compact_chunk<C::NW>(S, cnt);
-    if (f.active) len = keep_active<C::NW>(S, len);
-    bwd_chunk<C::NW, PPL, !EXACT>(S, acc, len, pxc, pyc0, g);
+    int len = compact_chunk<C>(S, cnt);
+    if (f.active) len = keep_active<C>(S, len);
+    list_run<C>(len, &kb, &ke);
+    bwd_chunk<C, PPL, !EXACT>(S, acc, kb, ke, pxc, pyc0, g);
     __syncthreads();
-    flush_grads<C::NT, C::NW, ONE>(S, acc, cnt, g_xy, g_chol, g_rgb);
+    flush_grads<C, ONE>(S, acc, cnt, g_xy, g_chol, g_rgb);
   }
 }
 

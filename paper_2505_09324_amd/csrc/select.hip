@@ -24,6 +24,8 @@
 namespace gs2d {
 namespace {
 
+constexpr int CH = 256;  // Gaussians staged per LDS chunk
+
 template <int NW>
 struct SelSmem {
   float4 A[CH];  // mx, my, l1, l2
@@ -54,7 +56,7 @@ k_select(int W, int H, int TX, const uint32_t *__restrict__ keys,
   const int tx = tile % TX, ty = tile / TX;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int px, py0;
-  pixel_of_thread<TILE, PPL>(tx, ty, &px, &py0);
+  pixel_of_thread<C, TILE, PPL>(tx, ty, &px, &py0);
   const size_t HW = (size_t)W * H;
   unsigned ch = 0;
 #pragma unroll

@@ -287,3 +287,36 @@ def test_fused_long_lists_every_variant():
         torch.cuda.synchronize()
         assert abs(float(loss) - want_loss) <= tol, (float(loss), want_loss, tol)
         assert_grads_close({"xy": host(g[0]), "chol": host(g[1]), "rgb": host(g[2])}, want)
+
+
+@pytest.mark.parametrize("W,H", [(400, 300), (640, 400), (1100, 1000)])
+def test_every_route_at_frame_sizes(W, H):
+    """Frames whose number of sub-blocks makes four, two or one wavefront
+    share a sub-block (every variant meets all three over the sizes), with
+    800 of 1500 Gaussians in one corner so that its lists take several LDS
+    chunks: pixels, losses and the gradients of both backward passes against
+    the oracle."""
+    N = 1500
+    xy, chol, rgb = synth.random_gaussians(N, W, H, seed=61, scale_lo=1.0, scale_hi=8.0)
+    xy[:800] = 20.0 + xy[:800] * (40.0 / W)
+    chol[:, 1] = np.random.default_rng(62).uniform(-3, 3, N).astype(np.float32)
+    rgb -= 0.5
+    frame, _ = synth.make_frame(W, H, seed=63)
+    ref = render_box(xy, chol, rgb, H, W)
+    want_loss, tol = mse(ref["img"], frame), loss_bound(ref, frame)
+    dl = dloss_dimg(ref["img"], frame)
+    want = gradients(xy, chol, rgb, dl, H, W)
+    P = [dev(xy), dev(chol), dev(rgb)]
+    for T, ppl in VARIANTS:
+        print(f"routes {W}x{H} T={T} ppl={ppl}", flush=True)
+        f = GpuFrame(W, H, N, T, max_pairs=400000, ppl=ppl)
+        img, _, loss = f.forward(*P, dev(frame))
+        assert_pixels_close(host(img), ref, what=f"T={T} ppl={ppl}")
+        g = [torch.zeros(N, d, device="cuda") for d in (2, 3, 3)]
+        floss = torch.empty((), device="cuda")
+        _lib.render_fused(f.shape, f.ws, P[2], dev(frame), *g, loss=floss)
+        b = f.backward(P[2], dev(dl.astype(np.float32)))
+        for x in (loss, floss):
+            assert abs(float(x) - want_loss) <= tol, (float(x), want_loss, tol)
+        for grads in (g, b):
+            assert_grads_close(dict(zip(("xy", "chol", "rgb"), map(host, grads))), want)

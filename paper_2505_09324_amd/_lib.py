@@ -233,7 +233,7 @@ def bins_view(shape: Shape, ws: torch.Tensor) -> Bins:
 
 def _slice(ws: torch.Tensor, ptr: int, count: int, dtype) -> torch.Tensor:
     off = ptr - ws.data_ptr()
-    nbytes = count * torch.empty((), dtype=dtype).element_size()
+    nbytes = count * dtype.itemsize
     return ws[off:off + nbytes].view(dtype)
 
 
@@ -254,6 +254,22 @@ def read_bins(shape: Shape, ws: torch.Tensor) -> dict:
         "n_culled": int(_slice(ws, b.n_culled, 1, torch.int32).item()),
         "n_tiles": b.n_tiles, "TX": b.tiles_x, "TY": b.tiles_y,
     }
+
+
+class BinStatus:
+    """The status word of the binning enqueued last on `ws`: its copy to the
+    host starts when the object is made, on the current stream, and value()
+    waits for that copy only."""
+
+    def __init__(self, shape: Shape, ws: torch.Tensor):
+        self._word = torch.empty(1, dtype=torch.int32, pin_memory=True)
+        self._word.copy_(_slice(ws, bins_view(shape, ws).status, 1, torch.int32), non_blocking=True)
+        self._done = torch.cuda.Event()
+        self._done.record()
+
+    def value(self) -> int:
+        self._done.synchronize()
+        return int(self._word)
 
 
 def project_bin(shape: Shape, xy, chol, ws):

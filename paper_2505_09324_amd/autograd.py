@@ -21,12 +21,12 @@ class GS2DRender(torch.autograd.Function):
         shape = _lib.make_shape(W, H, N, tile, max_pairs)
         ws = _lib.alloc_workspace(shape, xy.device)
         _lib.project_bin(shape, xy, chol, ws)
-        if check_overflow:
-            st = _lib.read_bins(shape, ws)["status"]
-            if st & _lib.STATUS_OVERFLOW:
-                raise _lib.GS2DError("gs2d_project_bin", _lib.GS2D_EOVERFLOW)
+        status = _lib.BinStatus(shape, ws) if check_overflow else None
         img = torch.empty(3, H, W, device=xy.device, dtype=torch.float32)
         _lib.render_fwd(shape, ws, rgb, img=img)
+        # the status word alone crosses to the host, while the render runs
+        if status is not None and status.value() & _lib.STATUS_OVERFLOW:
+            raise _lib.GS2DError("gs2d_project_bin", _lib.GS2D_EOVERFLOW)
         ctx.shape = shape
         ctx.ws = ws
         ctx.save_for_backward(xy, chol, rgb)

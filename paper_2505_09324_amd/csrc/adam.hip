@@ -146,6 +146,14 @@ __global__ void k_fill_zero(float *__restrict__ p, size_t n) {
     p[i] = 0.f;
 }
 
+__global__ void k_zero_grads(size_t N, float *__restrict__ g_xy, float *__restrict__ g_chol,
+                             float *__restrict__ g_rgb) {
+  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  if (i < 2 * N) g_xy[i] = 0.f;
+  else if (i < 5 * N) g_chol[i - 2 * N] = 0.f;
+  else if (i < 8 * N) g_rgb[i - 5 * N] = 0.f;
+}
+
 __global__ void k_fill_zero_u32(uint32_t *__restrict__ p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
        i += (size_t)gridDim.x * blockDim.x)
@@ -218,6 +226,13 @@ hipError_t launch_fill_zero(float *p, size_t n, hipStream_t st) {
   size_t nb = (n + 255) / 256;
   if (nb > 2048) nb = 2048;
   hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)nb), dim3(256), 0, st, p, n);
+  return hipGetLastError();
+}
+
+// The three gradient arrays of N Gaussians in one launch.
+hipError_t launch_zero_grads(int N, float *g_xy, float *g_chol, float *g_rgb, hipStream_t st) {
+  hipLaunchKernelGGL(k_zero_grads, dim3((unsigned)((8 * (size_t)N + 255) / 256)), dim3(256), 0, st,
+                     (size_t)N, g_xy, g_chol, g_rgb);
   return hipGetLastError();
 }
 

@@ -184,10 +184,7 @@ int gs2d_render_bwd(const gs2d_shape *shape, void *ws, size_t ws_bytes, const fl
     if (rc != GS2D_OK) return rc;
     if (!rgb || !dl_dimg || !g_xy || !g_chol || !g_rgb) return GS2D_EINVAL;
     hipStream_t st = as_stream(stream);
-    const size_t N = (size_t)L.N;
-    hipError_t e = launch_fill_zero(g_xy, 2 * N, st);
-    if (e == hipSuccess) e = launch_fill_zero(g_chol, 3 * N, st);
-    if (e == hipSuccess) e = launch_fill_zero(g_rgb, 3 * N, st);
+    hipError_t e = launch_zero_grads(L.N, g_xy, g_chol, g_rgb, st);
     if (e == hipSuccess) e = launch_render_bwd(L, ws, rgb, dl_dimg, g_xy, g_chol, g_rgb, st);
     return hip_status(e);
   } catch (...) {

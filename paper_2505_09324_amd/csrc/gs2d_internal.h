@@ -234,6 +234,7 @@ hipError_t launch_adam_extremes(const PendingAdam &a, int N, float *part, int32_
                                 hipStream_t st);
 
 hipError_t launch_fill_zero(float *p, size_t n, hipStream_t st);
+hipError_t launch_zero_grads(int N, float *g_xy, float *g_chol, float *g_rgb, hipStream_t st);
 
 // Quantisation (quant.hip): binary16 means, uniform min-max codes of the
 // Cholesky vector and colour; codes, ranges and bits nullable; qws holds

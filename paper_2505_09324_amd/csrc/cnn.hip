@@ -8,14 +8,14 @@
 // weights BF16 copies of FP32 master weights, accumulation FP32 on MFMA
 // (v_mfma_f32_16x16x32_bf16).
 //
-// Every convolution pass is an implicit GEMM C[M x N] = A[M x K] B[K x N]
-// whose operand tiles are staged in LDS as [row][k] (k contiguous, row pitch
-// padded so that the 16-byte reads of one MFMA step hit distinct banks) and
-// whose next stage is loaded into registers while the current one is
-// multiplied:
+// Every convolution pass is an implicit GEMM C[M x N] = A[M x K] B[K x N].
+// The forward pass reads its input from a patch of pixels in LDS; the backward
+// passes stage operand tiles in LDS as [row][k] (k contiguous, row pitch padded
+// so that the 16-byte reads of one MFMA step hit distinct banks).  What comes
+// next is loaded into registers while the current tile is multiplied:
 //   forward      M = Cout, N = output pixels, K = (tap, Cin)
-//                A = W[co][tap][ci], B = input gathered per tap (im2col);
-//                bias, ReLU and the BF16 rounding run in the epilogue
+//                A = W[co][tap][ci], B = the tap's input pixels; bias, ReLU
+//                and the BF16 rounding run in the epilogue
 //   grad input   M = Cin, N = input pixels of one stride-parity class,
 //                K = (the class's taps, Cout).  With stride 2 an input pixel
 //                (y, x) receives output gradients only through the taps
@@ -48,8 +48,8 @@ constexpr int NLAYER = 5;
 constexpr int HEAD_CH = 73;
 constexpr int NSLOT = 8, NPAR = 8;
 constexpr int KPAD = 32;     // K of the weight matrices is padded to one MFMA step
-constexpr int KS = 64;       // k per LDS stage (forward, grad input)
-constexpr int LP = KS + 8;   // its row pitch in halves (144 B = 9 x 16 B)
+constexpr int KS = 64;       // k per LDS stage (grad input)
+constexpr int LP = KS + 8;   // pitch in halves of its rows and of a pixel (144 B = 9 x 16 B)
 constexpr int PS = 128;      // output pixels per LDS stage (grad weight)
 constexpr int LPW = PS + 8;  // its row pitch in halves (272 B = 17 x 16 B)
 constexpr int GW_MIN_PIX = 4 * PS;  // smallest pixel range of a grad-weight block
@@ -110,93 +110,208 @@ __device__ __forceinline__ void mfma_step(const uint16_t *As, const uint16_t *Bs
 }
 
 // --------------------------------------------------------------- forward --
-// Workgroup tile 64 (Cout) x 32 WN (pixels); waves 2 x 2, each 32 x 16 WN.
-// Staging: A row t >> 2, k chunks (t & 3) * 8 and +32; B pixel rows
-// (t >> 3) + 32 j, k chunk (t & 7) * 8 (one tap and 8 channels: Cin % 8 == 0).
-template <int WN>
-__global__ void __launch_bounds__(256) k_conv_fwd(ConvArgs a) {
-  constexpr int BN = 32 * WN;
-  __shared__ __attribute__((aligned(16))) uint16_t As[64 * LP];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[BN * LP];
+// Bias, ReLU and rounding of a wave's 16 x 16 block: lane holds rows row ..
+// row + 3 of output pixel `col` (D[4 (lane >> 4) + r][lane & 15]).
+__device__ __forceinline__ void store_fwd(const ConvArgs &a, const floatx4 &acc, int row,
+                                          long long col, long long P) {
+  const ConvDims &d = a.d;
+  if (a.y) {
+    if (row < d.Cout) {  // Cout is a multiple of 4 for the hidden layers
+      uint16_t o[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float v = acc[r] + a.bias[row + r];
+        if (d.relu) v = fmaxf(v, 0.f);
+        o[r] = f2bf(v);
+      }
+      *reinterpret_cast<uint2 *>(a.y + col * d.Cout + row) = *reinterpret_cast<uint2 *>(o);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (row + r < d.Cout) a.y_planar[(size_t)(row + r) * P + col] = acc[r] + a.bias[row + r];
+  }
+}
+
+// First layer, from the frame itself.  A workgroup forms a 32 x 4 tile of
+// output pixels: it converts the 65 x 9 input pixels that the tile's taps
+// reach (RGB and residual as BF16, channels last, 16 bytes per pixel) into
+// LDS, writes those the tile owns to x_in (the backward pass reads them), and
+// multiplies straight from LDS, one tap of one pixel per 16-byte read; waves 2
+// x 2, each 32 channels x 64 pixels with its weights in registers.  The
+// output tile goes through LDS so that whole 128-byte pixels are stored.  HBM
+// bound: 150 MB at 1920 x 1080 (frame, residual, x_in and the output), 39 us.
+// As two launches, a conversion and an implicit GEMM that read x_in back 2.25
+// times, it took 17 + 37 us; with the output stored from the accumulators (32
+// bytes of a pixel at a time) 57 us.
+constexpr int C0_TW = 32, C0_TH = 4, C0_PW = 2 * C0_TW + 1, C0_PH = 2 * C0_TH + 1;
+constexpr int C0_N = C0_PW * C0_PH, C0_PER = (C0_N + 255) / 256;
+__global__ void __launch_bounds__(256)
+k_conv_first(ConvArgs a, const float *__restrict__ frame, const float *__restrict__ prev,
+             uint16_t *__restrict__ x_in) {
+  __shared__ __attribute__((aligned(16))) union {
+    uint4 px[C0_N];
+    uint16_t y[C0_TW * C0_TH * LP];
+  } sm;
   const ConvDims &d = a.d;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int m0 = blockIdx.y * 64;
-  const long long P = (long long)d.Hout * d.Wout;
-  const long long n0 = (long long)blockIdx.x * BN;
-  const int K = d.Kf;
-  const int ar = tid >> 2, ak = (tid & 3) * 8;
-  const uint16_t *wrow = a.w + (size_t)(m0 + ar) * K;
-  const int br = tid >> 3, bk = (tid & 7) * 8;
-  int iy0[WN], ix0[WN];
-  bool pv[WN];
+  const int tiles_x = (d.Wout + C0_TW - 1) / C0_TW;
+  const int ox0 = (blockIdx.x % tiles_x) * C0_TW, oy0 = (blockIdx.x / tiles_x) * C0_TH;
+  const size_t HW = (size_t)d.Hin * d.Win;
+  const int wm = w & 1, wn = w >> 1, r = lane & 15, kg = lane >> 4;
+  float f[C0_PER][3], q[C0_PER][3];
+  size_t at[C0_PER];
+  int own[C0_PER];
 #pragma unroll
-  for (int j = 0; j < WN; ++j) {
-    const long long p = n0 + br + 32 * j;
-    pv[j] = p < P;
-    const int oy = pv[j] ? (int)(p / d.Wout) : 0, ox = pv[j] ? (int)(p - (long long)oy * d.Wout) : 0;
-    iy0[j] = oy * d.stride - 1;
-    ix0[j] = ox * d.stride - 1;
+  for (int j = 0; j < C0_PER; ++j) {
+    const int e = tid + 256 * j, py = e / C0_PW, pxx = e - py * C0_PW;
+    const int iy = 2 * oy0 - 1 + py, ix = 2 * ox0 - 1 + pxx;
+    const bool in = e < C0_N && iy >= 0 && iy < d.Hin && ix >= 0 && ix < d.Win;
+    at[j] = (size_t)iy * d.Win + ix;
+    own[j] = in && py > 0 && pxx > 0;  // the first row and column belong to the tiles before
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      f[j][c] = in ? frame[c * HW + at[j]] : 0.f;
+      q[j][c] = prev ? (in ? prev[c * HW + at[j]] : 0.f) : f[j][c];
+    }
   }
-  uint4 ra[2], rb[WN];
-  auto load = [&](int k0) {
+  uint4 av[3][2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int k = k0 + ak + 32 * h;
-      ra[h] = (k < K) ? *reinterpret_cast<const uint4 *>(wrow + k) : make_uint4(0, 0, 0, 0);
-    }
-    const int k = k0 + bk;
-    const int tap = k / d.Cin, ci = k - tap * d.Cin;
-    const int ty = tap / 3, tx = tap - 3 * ty;
+  for (int ks = 0; ks < 3; ++ks)
 #pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      rb[j] = make_uint4(0, 0, 0, 0);
-      const int iy = iy0[j] + ty, ix = ix0[j] + tx;
-      if (pv[j] && k < K && tap < 9 && iy >= 0 && iy < d.Hin && ix >= 0 && ix < d.Win)
-        rb[j] = *reinterpret_cast<const uint4 *>(a.x + ((size_t)iy * d.Win + ix) * d.Cin + ci);
+    for (int i = 0; i < 2; ++i)
+      av[ks][i] = *reinterpret_cast<const uint4 *>(a.w + (size_t)(32 * wm + 16 * i + r) * d.Kf +
+                                                   32 * ks + 8 * kg);
+#pragma unroll
+  for (int j = 0; j < C0_PER; ++j) {
+    uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      v[c] = f2bf(f[j][c]);
+      v[3 + c] = f2bf(prev ? f[j][c] - q[j][c] : 0.f);
     }
-  };
-  floatx4 acc[2][WN];
+    if (tid + 256 * j < C0_N) sm.px[tid + 256 * j] = *reinterpret_cast<uint4 *>(v);
+    if (own[j]) *reinterpret_cast<uint4 *>(x_in + at[j] * 8) = *reinterpret_cast<uint4 *>(v);
+  }
+  __syncthreads();
+  floatx4 acc[2][4];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < WN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int wm = w & 1, wn = w >> 1;
-  load(0);
-  for (int k0 = 0; k0 < K; k0 += KS) {
-    __syncthreads();
-    *reinterpret_cast<uint4 *>(As + ar * LP + ak) = ra[0];
-    *reinterpret_cast<uint4 *>(As + ar * LP + ak + 32) = ra[1];
+    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < WN; ++j) *reinterpret_cast<uint4 *>(Bs + (br + 32 * j) * LP + bk) = rb[j];
-    __syncthreads();
-    if (k0 + KS < K) load(k0 + KS);
-    mfma_step<2, WN, LP>(As + 32 * wm * LP, Bs + 16 * WN * wn * LP, 0, lane, acc);
-    if (k0 + 32 < K) mfma_step<2, WN, LP>(As + 32 * wm * LP, Bs + 16 * WN * wn * LP, 32, lane, acc);
+  for (int ks = 0; ks < 3; ++ks) {
+    const int tap = 4 * ks + kg, ty = tap / 3, tx = tap - 3 * ty;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int oy = 2 * wn + (j >> 1), ox = 16 * (j & 1) + r;
+      uint4 b = make_uint4(0, 0, 0, 0);
+      if (tap < 9) b = sm.px[(2 * oy + ty) * C0_PW + 2 * ox + tx];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[ks][i]),
+                                                            __builtin_bit_cast(bf16x8, b),
+                                                            acc[i][j], 0, 0, 0);
+    }
   }
-  // lane holds D[4 (lane >> 4) + r][lane & 15] of each 16 x 16 block
+  __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = m0 + 32 * wm + 16 * i + 4 * (lane >> 4);
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      const long long col = n0 + 16 * WN * wn + 16 * j + (lane & 15);
-      if (col >= P) continue;
-      if (a.y) {
-        if (row < d.Cout) {  // Cout is a multiple of 4 for the hidden layers
-          uint16_t o[4];
+    for (int i = 0; i < 2; ++i) {
+      const int row = 32 * wm + 16 * i + 4 * kg;
+      const int p = 32 * (2 * wn + (j >> 1)) + 16 * (j & 1) + r;
+      uint16_t o[4];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            float v = acc[i][j][r] + a.bias[row + r];
-            if (d.relu) v = fmaxf(v, 0.f);
-            o[r] = f2bf(v);
-          }
-          *reinterpret_cast<uint2 *>(a.y + col * d.Cout + row) = *reinterpret_cast<uint2 *>(o);
-        }
-      } else {
+      for (int q4 = 0; q4 < 4; ++q4) o[q4] = f2bf(fmaxf(acc[i][j][q4] + a.bias[row + q4], 0.f));
+      *reinterpret_cast<uint2 *>(sm.y + p * LP + row) = *reinterpret_cast<uint2 *>(o);
+    }
+  __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (row + r < d.Cout) a.y_planar[(size_t)(row + r) * P + col] = acc[i][j][r] + a.bias[row + r];
+  for (int j = 0; j < 4; ++j) {
+    const int e = tid + 256 * j, p = e >> 3, c8 = 8 * (e & 7);
+    const int oy = oy0 + (p >> 5), ox = ox0 + (p & 31);
+    if (oy < d.Hout && ox < d.Wout)
+      *reinterpret_cast<uint4 *>(a.y + ((size_t)oy * d.Wout + ox) * 64 + c8) =
+          *reinterpret_cast<const uint4 *>(sm.y + p * LP + c8);
+  }
+}
+
+// Layers with 64 input channels.  A workgroup keeps its 64 rows of the weight
+// matrix in registers (16 rows x 576 per wave) and walks over 8 x 8 tiles of
+// output pixels.  A tile's input patch goes to LDS once and every tap is read
+// from there (pixel pitch 144 bytes: 16-byte reads of pixels at stride 2 spread
+// over the banks), while the next tile's patch loads into registers.  K runs
+// over (tap, channel) in steps of 32.  Bound by the loads of the patches: 26,
+// 11, 6.5 and 8.8 us for the four layers at 1920 x 1080.  As an implicit GEMM
+// staged tap by tap, each of its 9 stages waited for memory and every 64
+// pixels fetched the 74 KB of weights again: 30, 12, 8.2 and 8.9 us.  Waves of
+// 32 rows x 32 pixels halve the LDS reads, but their 144 registers of weights
+// leave no room for the patch (31 us; 28 us with the patch loaded straight to
+// a second LDS buffer, whose border tests triple the code).
+constexpr int CT = 8;  // output tile side
+template <int S>
+constexpr int CPATCH = (CT - 1) * S + 3;
+
+template <int S>
+__global__ void __launch_bounds__(256, 2) k_conv_fwd(ConvArgs a, int tiles_x, int n_tiles) {
+  constexpr int PW = CPATCH<S>, CHUNKS = PW * PW * 8, PER = (CHUNKS + 255) / 256;
+  __shared__ __attribute__((aligned(16))) uint16_t patch[PW * PW * LP];
+  const ConvDims &d = a.d;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int m0 = blockIdx.y * 64;
+  const int r = lane & 15, kg = lane >> 4;
+  uint4 v[PER];
+  auto load = [&](int t) {
+    const int iy0 = (t / tiles_x) * CT * S - 1, ix0 = (t % tiles_x) * CT * S - 1;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int e = tid + 256 * j, p = e >> 3, py = p / PW, px = p - py * PW;
+      const int iy = iy0 + py, ix = ix0 + px;
+      v[j] = make_uint4(0, 0, 0, 0);
+      if (e < CHUNKS && iy >= 0 && iy < d.Hin && ix >= 0 && ix < d.Win)
+        v[j] = *reinterpret_cast<const uint4 *>(a.x + ((size_t)iy * d.Win + ix) * 64 + 8 * (e & 7));
+    }
+  };
+  load(blockIdx.x);
+  uint4 av[18];
+#pragma unroll
+  for (int k = 0; k < 18; ++k)
+    av[k] = *reinterpret_cast<const uint4 *>(a.w + (size_t)(m0 + 16 * w + r) * d.Kf + 32 * k + 8 * kg);
+  const long long P = (long long)d.Hout * d.Wout;
+  for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int e = tid + 256 * j;
+      if (e < CHUNKS)
+        *reinterpret_cast<uint4 *>(patch + (e >> 3) * LP + 8 * (e & 7)) = v[j];
+    }
+    __syncthreads();
+    if (t + (int)gridDim.x < n_tiles) load(t + gridDim.x);
+    floatx4 acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // pixel r of 16-pixel block j: row 2 j + (r >> 3)
+    const uint16_t *base = patch + ((r >> 3) * S * PW + (r & 7) * S) * LP + 8 * kg;
+#pragma unroll
+    for (int k = 0; k < 18; ++k) {
+      const int tap = k >> 1, ty = tap / 3, tx = tap - 3 * ty;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint4 b = *reinterpret_cast<const uint4 *>(
+            base + ((2 * j * S + ty) * PW + tx) * LP + 32 * (k & 1));
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[k]),
+                                                         __builtin_bit_cast(bf16x8, b), acc[j], 0,
+                                                         0, 0);
       }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int oy = (t / tiles_x) * CT + 2 * j + (r >> 3);
+      const int ox = (t % tiles_x) * CT + (r & 7);
+      if (oy >= d.Hout || ox >= d.Wout) continue;
+      store_fwd(a, acc[j], m0 + 16 * w + 4 * kg, (long long)oy * d.Wout + ox, P);
     }
   }
 }
@@ -501,24 +616,6 @@ k_gw_reduce(ConvDims d, int splits, int ntile_n, const float *__restrict__ gpart
   }
 }
 
-// Frame (+ residual) -> channels-last bf16 input [H*W][8].
-__global__ void __launch_bounds__(256)
-k_cnn_input(int H, int W, const float *__restrict__ frame, const float *__restrict__ prev,
-            uint16_t *__restrict__ x) {
-  const size_t HW = (size_t)H * W;
-  for (size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x; p < HW;
-       p += (size_t)gridDim.x * blockDim.x) {
-    uint16_t v[8];
-    for (int c = 0; c < 3; ++c) {
-      const float f = frame[c * HW + p];
-      v[c] = f2bf(f);
-      v[3 + c] = f2bf(prev ? f - prev[c * HW + p] : 0.f);
-    }
-    v[6] = v[7] = 0;
-    *reinterpret_cast<uint4 *>(x + p * 8) = *reinterpret_cast<uint4 *>(v);
-  }
-}
-
 __device__ inline float sigm(float z) { return 1.f / (1.f + __expf(-z)); }
 
 // Per-tile loss: CE over the 9 count logits + Chamfer between the first k
@@ -767,16 +864,14 @@ static int pick_wn(long long pixels, int mtiles, long long min_blocks) {
   return 1;
 }
 
-// Forward: 64-pixel tiles where they still give >= 2000 workgroups, else
-// 32 (measured at 1080p: 128-pixel tiles are slower on every layer).
+// 512 workgroups of k_conv_fwd are resident (two per compute unit), shared by
+// the M tiles.
 static hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t st) {
   const ConvDims &d = a.d;
-  const long long P = (long long)d.Hout * d.Wout;
-  const int mt = d.Mpad / 64, wn = std::min(2, pick_wn(P, mt, 2000));
-  const dim3 g((unsigned)((P + 32 * wn - 1) / (32 * wn)), (unsigned)mt);
-  if (wn == 4) hipLaunchKernelGGL(k_conv_fwd<4>, g, dim3(256), 0, st, a);
-  else if (wn == 2) hipLaunchKernelGGL(k_conv_fwd<2>, g, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL(k_conv_fwd<1>, g, dim3(256), 0, st, a);
+  const int tx = (d.Wout + CT - 1) / CT, n = tx * ((d.Hout + CT - 1) / CT), mt = d.Mpad / 64;
+  const dim3 g((unsigned)std::min(n, 512 / mt), (unsigned)mt);
+  if (d.stride == 2) hipLaunchKernelGGL(k_conv_fwd<2>, g, dim3(256), 0, st, a, tx, n);
+  else hipLaunchKernelGGL(k_conv_fwd<1>, g, dim3(256), 0, st, a, tx, n);
   return hipGetLastError();
 }
 
@@ -1436,8 +1531,6 @@ int gs2d_cnn_forward(int32_t H, int32_t W, const float *frame, const float *prev
   if (ws_bytes < C.total) return GS2D_ENOSPACE;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   uint16_t *x = at<uint16_t>(ws, C.x_in);
-  hipLaunchKernelGGL(k_cnn_input, dim3((unsigned)std::min<size_t>(((size_t)H * W + 255) / 256, 8192)),
-                     dim3(256), 0, st, H, W, frame, prev, x);
   const uint16_t *in = x;
   for (int i = 0; i < NLAYER; ++i) {
     ConvArgs a = {};
@@ -1451,8 +1544,17 @@ int gs2d_cnn_forward(int32_t H, int32_t W, const float *frame, const float *prev
     } else {
       a.y_planar = at<float>(ws, C.head);
     }
-    if (launch_conv_fwd(a, st) != hipSuccess) return GS2D_EHIP;
+    if (i == 0) {
+      const ConvDims &d = a.d;
+      hipLaunchKernelGGL(k_conv_first,
+                         dim3((unsigned)((d.Wout + C0_TW - 1) / C0_TW) *
+                              (unsigned)((d.Hout + C0_TH - 1) / C0_TH)),
+                         dim3(256), 0, st, a, frame, prev, x);
+    } else if (launch_conv_fwd(a, st) != hipSuccess) {
+      return GS2D_EHIP;
+    }
   }
+  if (hipGetLastError() != hipSuccess) return GS2D_EHIP;
   if (head_out &&
       hipMemcpyAsync(head_out, at<float>(ws, C.head), sizeof(float) * HEAD_CH * C.n_tiles,
                      hipMemcpyDeviceToDevice, st) != hipSuccess)

@@ -430,3 +430,10 @@ def test_cnn_adam_matches_oracle_decoupled_decay():
                 np.testing.assert_array_equal(wt[:, tap * cs:tap * cs + d["Cout"]], want)
         wb_off += M.size
         wt_off += d["Cin"] * kb
+
+
+# layer 0 in tiles of 32 x 4 outputs, the others of 8 x 8: filled exactly, one
+# row and column more, one less
+@pytest.mark.parametrize("hw", [(64, 64), (66, 130), (60, 124)])
+def test_layers_at_tile_edges(hw):
+    test_layers_elementwise_against_oracle(hw)

@@ -24,13 +24,10 @@
 //                no multiply-by-zero is issued.  The epilogue applies the
 //                previous layer's ReLU' and writes its BF16 dZ directly.
 //   grad weight  M = Cout, N = (tap, Cin), K = output pixels, split over
-//                workgroups whose partial tiles a second kernel sums (plain
-//                stores: FP32 atomics from every workgroup cost more than the
-//                GEMM).  Both
-//                operands are channels-last in memory and pixel-contiguous in
-//                LDS: each thread loads an 8 pixel x 8 channel block and
-//                transposes it in registers.  The blocks of the first N tile
-//                also sum dZ over their pixels: the bias gradient.
+//                workgroups whose partials a second kernel sums (plain stores:
+//                FP32 atomics from every workgroup cost more than the GEMM).
+//                Both operands are channels-last; LDS reads that transpose
+//                make fragments of them.  dZ times ones is the bias gradient.
 // dZ = dL/d(layer output) masked by ReLU', held as BF16 [pixels][CoutS].
 #include <algorithm>
 #include <cmath>
@@ -50,9 +47,6 @@ constexpr int NSLOT = 8, NPAR = 8;
 constexpr int KPAD = 32;     // K of the weight matrices is padded to one MFMA step
 constexpr int KS = 64;       // k per LDS stage (grad input)
 constexpr int LP = KS + 8;   // pitch in halves of its rows and of a pixel (144 B = 9 x 16 B)
-constexpr int PS = 128;      // output pixels per LDS stage (grad weight)
-constexpr int LPW = PS + 8;  // its row pitch in halves (272 B = 17 x 16 B)
-constexpr int GW_MIN_PIX = 4 * PS;  // smallest pixel range of a grad-weight block
 
 __device__ inline uint16_t f2bf(float x) {  // round to nearest even
   const uint32_t u = __float_as_uint(x);
@@ -78,10 +72,6 @@ struct ConvArgs {
   float *y_planar;       // forward output [Cout][Hout*Wout] fp32 (head)
   const uint16_t *dz;    // dZ of this layer [Hout*Wout][CoutS] bf16
   uint16_t *dz_prev;     // grad input: dZ of the previous layer [Hin*Win][Cin] bf16
-  float *gpart;          // grad weight: partial tiles [work][64 col][64 row] fp32
-  float *bpart;          // grad weight: bias partials [split][M tile][64] fp32
-  int ksplit;            // grad weight: output pixels per workgroup (multiple of PS)
-  int ntile_n, nwork;    // grad weight: N tiles, real workgroups (grid rounded up to 8)
   int ncls;              // grad input: parity classes (4 for stride 2, else 1)
   int cls_tile0[5];      // grad input: first workgroup of each class, then the total
 };
@@ -461,159 +451,312 @@ __global__ void __launch_bounds__(256) k_conv_bwd_data(ConvArgs a) {
 }
 
 // ----------------------------------------------------------- grad weight --
-__device__ __forceinline__ uint32_t u4_at(const uint4 &u, int i) {
-  return i == 0 ? u.x : i == 1 ? u.y : i == 2 ? u.z : u.w;
+// dW[co][tap][ci] = sum over output pixels of dZ[pixel][co] x[tap's pixel][ci]:
+// K runs over pixels, but both operands are channels-last.  They are staged in
+// LDS as they lie in memory (a tile of dZ and the patch of x that its taps
+// reach) and read with ds_read_b64_tr_b16, which hands each lane 4 pixels of
+// one channel: 16 lanes read 4 pixels x 16 channels, every lane from an address
+// of its own, so a tap is an offset into the patch.  One MFMA step covers 4
+// rows x 8 pixels; lane group kg = lane >> 4 takes row kg, half h pixels 4 h ..
+// 4 h + 3.  dZ outside the image is zero; a lane whose output pixel lies outside
+// reads x from a zeroed part of LDS instead (0 times infinity would not be 0).
+// The pitches put the 8 pixels that 32 lanes read on distinct banks.
+//
+// HBM and latency bound.  At 1920 x 1080 the 64-channel layers take 40 us (126
+// MB with the partials), the first layer 20 us (100 MB and 9 MB of partials),
+// the sums 14 us.  As GEMMs over 64 x 64 tiles that transposed in registers on
+// their way to LDS, every column tile read dZ again and every tap its pixels
+// of x (300 MB through L2 for the second layer alone): 44, 18, 12 and 13 us,
+// the first layer 40 us, five sums 32 us.
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef short short8v __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) short4v lds_short4;
+__device__ __forceinline__ bf16x8 read_tr(const uint8_t *lo, const uint8_t *hi) {
+  const short4v a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)lo);
+  const short4v b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)hi);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ bf16x8 bf_ones() {
+  return __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
 }
 
-// Workgroup tile 64 (Cout) x 64 (tap, Cin) over a range of ksplit output
-// pixels, PS per stage; waves 2 x 2, each 32 x 32; the tile goes to gpart.  Threads 0..127 stage A
-// (dZ), 128..255 stage B (the input gathered at the tile's tap); thread
-// chunk: 8 channels (group g = c >> 4) x 8 pixels (group q = c & 15).  The
-// 1D grid is ordered so that the N tiles of one pixel range are consecutive
-// work items on one XCD (workgroup b runs on XCD b % 8): dZ of that range is
-// fetched into one L2.
-__global__ void __launch_bounds__(256) k_conv_bwd_weight(ConvArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[64 * LPW];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[64 * LPW];
-  const ConvDims &d = a.d;
+// One layer's share of the grad-weight work: splits of `per` tiles, each with
+// a partial [M tile][columns + 1][64 rows] in part (the last column is the
+// bias gradient: dZ times ones).
+struct GwLayer {
+  const uint16_t *x, *dz;
+  float *part, *dw, *db;
+  int Hin, Win, Hout, Wout, Cout, CoutS, Kf;
+  int cols, mt, tiles_x, n_tiles, per, splits, work0;
+};
+struct GwArgs {
+  GwLayer L[NLAYER];
+  int nwork;  // work items of layers 1 .. 4
+};
+
+constexpr int GZ_PIX = 160, GZ_ROW = 8 * GZ_PIX + 128;  // dZ tile: bytes per pixel, per row
+
+// Adds the accumulators of the waves of the second half of the workgroup's K
+// range to those of the first, through LDS.
+template <int N>
+__device__ __forceinline__ void gw_combine(floatx4 (&acc)[N], bool second, float4 *lds, int lane,
+                                           int slots) {
+  __syncthreads();
+  if (second) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      lds[i * slots + lane] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+  }
+  __syncthreads();
+  if (!second) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float4 v = lds[i * slots + lane];
+      acc[i] += floatx4{v.x, v.y, v.z, v.w};
+    }
+  }
+}
+
+// Layers with 64 input channels: a workgroup of 8 waves takes 64 rows (co) x 9
+// taps x 32 channels over a range of 8 x 8 pixel tiles: waves 2 (32 rows) x 2
+// (16 channels) x 2 (upper and lower half of the tile).  Two LDS buffers, and
+// the tile after next on its way in registers.
+constexpr int GW_LDS = 73728 + 2 * 4096, GW_ZERO = 3328;  // combine buffer; zeroed part
+template <int S>
+__device__ __forceinline__ void gw_layer(const GwLayer &L, int work, uint8_t *lds) {
+  constexpr int PW = 7 * S + 3, PIX = S == 2 ? 80 : 96, ROW = S == 2 ? 1472 : 1152;
+  constexpr int BUF = PW * ROW + 8 * GZ_ROW, NX = PW * PW * 4, PER = (NX + 511) / 512;
+  static_assert(2 * BUF <= GW_LDS && 2 * ROW + 2 * PIX + 64 <= GW_ZERO, "LDS");
+  const int half = work & 1, mt = (work >> 1) % L.mt, split = (work >> 1) / L.mt;
+  const int m0 = 64 * mt, t0 = split * L.per, t1 = min(L.n_tiles, t0 + L.per);
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int wm = w & 1, wn = (w >> 1) & 1, g = w >> 2, i16 = lane & 15, kg = lane >> 4;
+  struct Stage {
+    uint4 x[PER], z;
+  };
+  auto load = [&](Stage &v, int t) {
+    const int oy0 = t / L.tiles_x * 8, ox0 = t % L.tiles_x * 8;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int e = tid + 512 * j, p = e >> 2, py = p / PW, px = p - py * PW;
+      const int iy = oy0 * S - 1 + py, ix = ox0 * S - 1 + px;
+      v.x[j] = make_uint4(0, 0, 0, 0);
+      if (e < NX && iy >= 0 && iy < L.Hin && ix >= 0 && ix < L.Win)
+        v.x[j] = *reinterpret_cast<const uint4 *>(L.x + ((size_t)iy * L.Win + ix) * 64 + 32 * half +
+                                                  8 * (e & 3));
+    }
+    const int p = tid >> 3, oy = oy0 + (p >> 3), ox = ox0 + (p & 7), co = m0 + 8 * (tid & 7);
+    v.z = make_uint4(0, 0, 0, 0);
+    if (oy < L.Hout && ox < L.Wout && co < L.CoutS)
+      v.z = *reinterpret_cast<const uint4 *>(L.dz + ((size_t)oy * L.Wout + ox) * L.CoutS + co);
+  };
+  auto put = [&](const Stage &v, uint8_t *buf) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int e = tid + 512 * j, p = e >> 2, py = p / PW, px = p - py * PW;
+      if (e < NX) *reinterpret_cast<uint4 *>(buf + py * ROW + px * PIX + 16 * (e & 3)) = v.x[j];
+    }
+    const int p = tid >> 3;
+    *reinterpret_cast<uint4 *>(buf + PW * ROW + (p >> 3) * GZ_ROW + (p & 7) * GZ_PIX +
+                               16 * (tid & 7)) = v.z;
+  };
+  floatx4 acc[20];  // [tap][row block], then the bias of the two row blocks
+#pragma unroll
+  for (int i = 0; i < 20; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int row = 4 * g + kg, col = i16 >> 2;
+  const bool bias = half == 0 && wn == 0;
+  auto tile = [&](const uint8_t *buf, int t) {
+    const int oy = t / L.tiles_x * 8 + row, ox = t % L.tiles_x * 8 + col;
+    const uint8_t *zb = buf + PW * ROW + row * GZ_ROW + col * GZ_PIX + 64 * wm + 8 * (i16 & 3);
+    const uint8_t *xb = buf + row * S * ROW + col * S * PIX, *none = lds + GW_LDS;
+    const int c = 32 * wn + 8 * (i16 & 3);
+    const uint8_t *x0 = (oy < L.Hout && ox < L.Wout ? xb : none) + c;
+    const uint8_t *x1 = (oy < L.Hout && ox + 4 < L.Wout ? xb + 4 * S * PIX : none) + c;
+    bf16x8 av[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) av[i] = read_tr(zb + 32 * i, zb + 32 * i + 4 * GZ_PIX);
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      const int o = tap / 3 * ROW + tap % 3 * PIX;
+      const bf16x8 bv = read_tr(x0 + o, x1 + o);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        acc[2 * tap + i] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv, acc[2 * tap + i], 0, 0, 0);
+    }
+    if (bias)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        acc[18 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bf_ones(), acc[18 + i], 0, 0, 0);
+  };
+  uint8_t *b0 = lds, *b1 = lds + BUF;
+  for (int e = tid; e < GW_ZERO / 4; e += 512) reinterpret_cast<uint32_t *>(lds + GW_LDS)[e] = 0;
+  Stage va, vb;
+  load(va, t0);
+  if (t0 + 1 < t1) load(vb, t0 + 1);
+  put(va, b0);
+  __syncthreads();
+  // a buffer is written between the barrier after its last read and the one
+  // before its next
+  for (int t = t0; t < t1; t += 2) {
+    if (t + 2 < t1) load(va, t + 2);
+    tile(b0, t);
+    if (t + 1 >= t1) break;
+    put(vb, b1);
+    __syncthreads();
+    if (t + 3 < t1) load(vb, t + 3);
+    tile(b1, t + 1);
+    if (t + 2 >= t1) break;
+    put(va, b0);
+    __syncthreads();
+  }
+  gw_combine(acc, g == 1, reinterpret_cast<float4 *>(lds), tid & 255, 256);
+  if (g == 1) return;
+  float *part = L.part + ((size_t)split * L.mt + mt) * (L.cols + 1) * 64 + 32 * wm + 4 * kg;
+#pragma unroll
+  for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const floatx4 &v = acc[2 * tap + i];
+      *reinterpret_cast<float4 *>(part + (64 * tap + 32 * half + 16 * wn + i16) * 64 + 16 * i) =
+          make_float4(v[0], v[1], v[2], v[3]);
+    }
+  if (bias && i16 == 0)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      *reinterpret_cast<float4 *>(part + L.cols * 64 + 16 * i) =
+          make_float4(acc[18 + i][0], acc[18 + i][1], acc[18 + i][2], acc[18 + i][3]);
+}
+
+// Layers 1 .. 4 in one launch of at most 256 workgroups, one per compute unit,
+// of equally many tiles each: a layer alone leaves most units idle (the fourth
+// has 135 tiles at 1920 x 1080), and fewer splits mean fewer partials (18 MB).  The grid is ordered so that the two channel
+// halves of a range of tiles run at the same time on one XCD (workgroup b is on
+// XCD b % 8) and share dZ and the 128-byte pixels in its L2.
+__global__ void __launch_bounds__(512, 2) k_conv_bwd_weight(GwArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[GW_LDS + GW_ZERO];
   const int per_xcd = (int)(gridDim.x >> 3);
   const int work = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
   if (work >= a.nwork) return;
-  const int ntm = d.Mpad / 64;
-  const int nt = work % a.ntile_n, mt = (work / a.ntile_n) % ntm, split = work / (a.ntile_n * ntm);
-  const int m0 = mt * 64, n0 = nt * 64;
-  const long long P = (long long)d.Hout * d.Wout;
-  const long long kbeg = (long long)split * a.ksplit, kend = min(P, kbeg + a.ksplit);
+  int l = 1;
+  while (l + 1 < NLAYER && work >= a.L[l + 1].work0) ++l;
+  if (l == NLAYER - 1) gw_layer<1>(a.L[NLAYER - 1], work - a.L[NLAYER - 1].work0, lds);
+  else gw_layer<2>(a.L[l], work - a.L[l].work0, lds);
+}
+
+// First layer (8 input channels): 64 rows x 72 columns (tap, ci) over a range
+// of 8 x 16 pixel tiles; 16 columns are two taps, which a lane selects by the
+// address it reads.  4 waves: 2 (32 rows) x 2 (upper and lower half).
+constexpr int G0_ROW = 320, G0_X = 33 * G0_ROW, G0_BUF = G0_X + 16 * GZ_ROW, G0_ZERO = 768;
+__global__ void __launch_bounds__(256, 2) k_conv_bwd_weight_first(GwLayer L) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[G0_BUF + G0_ZERO];
+  constexpr int NX = 33 * 17, PER = (NX + 255) / 256;
+  static_assert(2 * G0_ROW + 2 * 16 + 32 <= G0_ZERO && 12 * 2048 <= G0_BUF, "LDS");
+  const int t0 = blockIdx.x * L.per, t1 = min(L.n_tiles, t0 + L.per);
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const bool isA = tid < 128;
-  const int ch = tid & 127, q = ch & 15, g = ch >> 4;
-  // A: channels co0 .. co0 + 7 of dZ; B: columns n .. n + 7 = one tap, 8 channels
-  const int co0 = m0 + 8 * g;
-  const int n = n0 + 8 * g, tap = n / d.Cin, ci = n - tap * d.Cin;
-  const int ty = tap / 3, tx = tap - 3 * ty;
-  const bool colok = isA ? (co0 < d.CoutS) : (n < d.Kf && tap < 9);
-  const bool do_bias = isA && nt == 0;
-  uint4 v[8];
-  auto load = [&](long long k0) {
-    const long long p0 = k0 + 8 * q;
-    if (isA) {
+  const int wm = w & 1, g = w >> 1, i16 = lane & 15, kg = lane >> 4;
+  uint4 vx[PER], vz[4];
+  auto load = [&](int t) {
+    const int oy0 = t / L.tiles_x * 16, ox0 = t % L.tiles_x * 8;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const long long p = p0 + j;
-        v[j] = (colok && p < kend)
-                   ? *reinterpret_cast<const uint4 *>(a.dz + p * d.CoutS + co0)
-                   : make_uint4(0, 0, 0, 0);
-      }
-    } else {
-      int oy = (int)(min(p0, P - 1) / d.Wout);
-      int ox = (int)(min(p0, P - 1) - (long long)oy * d.Wout);
+    for (int j = 0; j < PER; ++j) {
+      const int e = tid + 256 * j, py = e / 17, px = e - py * 17;
+      const int iy = oy0 * 2 - 1 + py, ix = ox0 * 2 - 1 + px;
+      vx[j] = make_uint4(0, 0, 0, 0);
+      if (e < NX && iy >= 0 && iy < L.Hin && ix >= 0 && ix < L.Win)
+        vx[j] = *reinterpret_cast<const uint4 *>(L.x + ((size_t)iy * L.Win + ix) * 8);
+    }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        v[j] = make_uint4(0, 0, 0, 0);
-        const int iy = oy * d.stride + ty - 1, ix = ox * d.stride + tx - 1;
-        if (colok && p0 + j < kend && iy >= 0 && iy < d.Hin && ix >= 0 && ix < d.Win)
-          v[j] = *reinterpret_cast<const uint4 *>(a.x + ((size_t)iy * d.Win + ix) * d.Cin + ci);
-        if (++ox == d.Wout) {
-          ox = 0;
-          ++oy;
-        }
-      }
+    for (int j = 0; j < 4; ++j) {
+      const int p = (tid >> 3) + 32 * j, oy = oy0 + (p >> 3), ox = ox0 + (p & 7);
+      vz[j] = make_uint4(0, 0, 0, 0);
+      if (oy < L.Hout && ox < L.Wout)
+        vz[j] = *reinterpret_cast<const uint4 *>(L.dz + ((size_t)oy * L.Wout + ox) * 64 + 8 * (tid & 7));
     }
   };
-  float bsum[8];
+  floatx4 acc[12];  // [column block][row block], then the bias
 #pragma unroll
-  for (int r = 0; r < 8; ++r) bsum[r] = 0.f;
-  floatx4 acc[2][2];
+  for (int i = 0; i < 12; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  int off[5];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int wm = w & 1, wn = w >> 1;
-  uint16_t *dst = (isA ? As : Bs) + 8 * g * LPW + 8 * q;
-  load(kbeg);
-  for (long long k0 = kbeg; k0 < kend; k0 += PS) {
+  for (int n = 0; n < 5; ++n) {
+    const int tap = min(8, 2 * n + ((i16 >> 1) & 1));
+    off[n] = tap / 3 * G0_ROW + tap % 3 * 16 + 8 * (i16 & 1);
+  }
+  for (int e = tid; e < G0_ZERO / 4; e += 256) reinterpret_cast<uint32_t *>(lds + G0_BUF)[e] = 0;
+  load(t0);
+  for (int t = t0; t < t1; ++t) {
     __syncthreads();
-    // 8 x 8 transpose: row 2i + (0|1) of channel pair i = the even / odd
-    // halves of dword i of the 8 pixels
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      uint32_t lo[4], hi[4];
+    for (int j = 0; j < PER; ++j) {
+      const int e = tid + 256 * j, py = e / 17, px = e - py * 17;
+      if (e < NX) *reinterpret_cast<uint4 *>(lds + py * G0_ROW + px * 16) = vx[j];
+    }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t e = u4_at(v[2 * j], i), o = u4_at(v[2 * j + 1], i);
-        lo[j] = (e & 0xFFFFu) | (o << 16);
-        hi[j] = (e >> 16) | (o & 0xFFFF0000u);
-      }
-      *reinterpret_cast<uint4 *>(dst + (2 * i) * LPW) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-      *reinterpret_cast<uint4 *>(dst + (2 * i + 1) * LPW) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-      if (do_bias) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          bsum[2 * i] += __uint_as_float(lo[j] << 16) + __uint_as_float(lo[j] & 0xFFFF0000u);
-          bsum[2 * i + 1] += __uint_as_float(hi[j] << 16) + __uint_as_float(hi[j] & 0xFFFF0000u);
-        }
-      }
+    for (int j = 0; j < 4; ++j) {
+      const int p = (tid >> 3) + 32 * j;
+      *reinterpret_cast<uint4 *>(lds + G0_X + (p >> 3) * GZ_ROW + (p & 7) * GZ_PIX + 16 * (tid & 7)) =
+          vz[j];
     }
     __syncthreads();
-    if (k0 + PS < kend) load(k0 + PS);
-    const int nsub = (int)min((long long)(PS / 32), (kend - k0 + 31) / 32);
+    if (t + 1 < t1) load(t + 1);
 #pragma unroll
-    for (int s = 0; s < PS / 32; ++s)
-      if (s < nsub) mfma_step<2, 2, LPW>(As + 32 * wm * LPW, Bs + 32 * wn * LPW, 32 * s, lane, acc);
-  }
-  if (do_bias) {  // lanes 16 k .. 16 k + 15 share the channel group
+    for (int s = 0; s < 2; ++s) {
+      const int row = 8 * g + 4 * s + kg, col = i16 >> 2;
+      const int oy = t / L.tiles_x * 16 + row, ox = t % L.tiles_x * 8 + col;
+      const uint8_t *zb = lds + G0_X + row * GZ_ROW + col * GZ_PIX + 64 * wm + 8 * (i16 & 3);
+      const uint8_t *xb = lds + row * 2 * G0_ROW + col * 32, *none = lds + G0_BUF;
+      const uint8_t *x0 = oy < L.Hout && ox < L.Wout ? xb : none;
+      const uint8_t *x1 = oy < L.Hout && ox + 4 < L.Wout ? xb + 128 : none;
+      bf16x8 av[2];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      float s = bsum[r];
-      s += __shfl_xor(s, 1, 64);
-      s += __shfl_xor(s, 2, 64);
-      s += __shfl_xor(s, 4, 64);
-      s += __shfl_xor(s, 8, 64);
-      if (q == 0) a.bpart[((size_t)split * ntm + mt) * 64 + 8 * g + r] = s;
+      for (int i = 0; i < 2; ++i) av[i] = read_tr(zb + 32 * i, zb + 32 * i + 4 * GZ_PIX);
+#pragma unroll
+      for (int n = 0; n < 5; ++n) {
+        const bf16x8 bv = read_tr(x0 + off[n], x1 + off[n]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          acc[2 * n + i] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv, acc[2 * n + i], 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        acc[10 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bf_ones(), acc[10 + i], 0, 0, 0);
     }
   }
-  // partial tile, column-major: the 4 rows a lane holds are contiguous
-  float *pt = a.gpart + (size_t)work * 4096;
+  gw_combine(acc, g == 1, reinterpret_cast<float4 *>(lds), tid & 127, 128);
+  if (g == 1) return;
+  float *part = L.part + (size_t)blockIdx.x * 73 * 64 + 32 * wm + 4 * kg;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = 32 * wm + 16 * i + 4 * (lane >> 4);
+  for (int n = 0; n < 6; ++n) {
+    const int c = 16 * n + i16;  // block 5 is the bias: its columns are equal
+    if (n < 5 ? c < 72 : i16 == 0)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = 32 * wn + 16 * j + (lane & 15);
-      *reinterpret_cast<float4 *>(pt + col * 64 + row) =
-          make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-    }
+      for (int i = 0; i < 2; ++i)
+        *reinterpret_cast<float4 *>(part + min(c, 72) * 64 + 16 * i) =
+            make_float4(acc[2 * n + i][0], acc[2 * n + i][1], acc[2 * n + i][2], acc[2 * n + i][3]);
   }
 }
 
-// Sum of the grad-weight partial tiles over the pixel splits, added into dW
-// (and the bias partials into dbias).  Grid x: 16 workgroups per 64 x 64
-// tile (one element per thread), then one per M tile for the bias; grid y:
-// chunks of GW_CHUNK splits, combined with FP32 atomics.
-constexpr int GW_CHUNK = 32;
-__global__ void __launch_bounds__(256)
-k_gw_reduce(ConvDims d, int splits, int ntile_n, const float *__restrict__ gpart,
-            const float *__restrict__ bpart, float *__restrict__ dw, float *__restrict__ db) {
-  const int ntm = d.Mpad / 64, tiles = ntile_n * ntm;
-  const int s0 = blockIdx.y * GW_CHUNK, s1 = min(splits, s0 + GW_CHUNK);
-  const int tid = threadIdx.x;
-  if ((int)blockIdx.x < 16 * tiles) {
-    const int tile = blockIdx.x >> 4, e = (blockIdx.x & 15) * 256 + tid;
-    const int row = (tile / ntile_n) * 64 + (e & 63), col = (tile % ntile_n) * 64 + (e >> 6);
-    if (row >= d.Cout || col >= d.Kf) return;
-    const float *src = gpart + (size_t)tile * 4096 + e;
-    float sum = 0.f;
+// Sum of the partials over the splits, added into dW and dbias: one workgroup
+// per column (64 rows) of every layer, four lanes' worth of splits each.
+__global__ void __launch_bounds__(256) k_gw_reduce(GwArgs a) {
+  __shared__ float red[256];
+  int b = blockIdx.x, l = 0;
+  while (b >= a.L[l].mt * (a.L[l].cols + 1)) b -= a.L[l].mt * (a.L[l].cols + 1), ++l;
+  const GwLayer &L = a.L[l];
+  const int tid = threadIdx.x, mt = b / (L.cols + 1), c = b - mt * (L.cols + 1);
+  const size_t stride = (size_t)L.mt * (L.cols + 1) * 64;
+  const float *src = L.part + (size_t)b * 64 + (tid & 63);
+  float sum = 0.f;
 #pragma unroll 8
-    for (int sp = s0; sp < s1; ++sp) sum += src[(size_t)sp * tiles * 4096];
-    if (sum != 0.f) atomicAdd(&dw[(size_t)row * d.Kf + col], sum);
-  } else {
-    const int mt = blockIdx.x - 16 * tiles, co = mt * 64 + tid;
-    if (tid >= 64 || co >= d.Cout) return;
-    float sum = 0.f;
-#pragma unroll 8
-    for (int sp = s0; sp < s1; ++sp) sum += bpart[((size_t)sp * ntm + mt) * 64 + tid];
-    if (sum != 0.f) atomicAdd(&db[co], sum);
-  }
+  for (int s = tid >> 6; s < L.splits; s += 4) sum += src[s * stride];
+  red[tid] = sum;
+  __syncthreads();
+  const int r = 64 * mt + tid;
+  if (tid >= 64 || r >= L.Cout) return;
+  sum = (red[tid] + red[tid + 64]) + (red[tid + 128] + red[tid + 192]);
+  if (sum != 0.f) atomicAdd(c < L.cols ? &L.dw[(size_t)r * L.Kf + c] : &L.db[r], sum);
 }
 
 __device__ inline float sigm(float z) { return 1.f / (1.f + __expf(-z)); }
@@ -756,24 +899,6 @@ k_loss_sum(int n_tiles, const float *__restrict__ tile_loss, const int *__restri
 }  // namespace
 
 // ------------------------------------------------------------ layout ----
-// Grad-weight work split: about 1024 workgroups (split x tile), each over a
-// multiple of PS and at least GW_MIN_PIX output pixels.
-struct GwSplit {
-  int ntile_n, tiles, ksplit, splits;
-};
-static GwSplit gw_split(const ConvDims &d) {
-  GwSplit g;
-  const long long P = (long long)d.Hout * d.Wout;
-  g.ntile_n = (d.Kf + 63) / 64;
-  g.tiles = g.ntile_n * (d.Mpad / 64);
-  const long long want = std::max(1, 1024 / g.tiles);
-  long long ks = (P + want - 1) / want;
-  ks = std::max<long long>(GW_MIN_PIX, (ks + PS - 1) / PS * PS);
-  g.ksplit = (int)ks;
-  g.splits = (int)((P + ks - 1) / ks);
-  return g;
-}
-
 struct CnnLayout {
   int H, W;
   ConvDims L[NLAYER];
@@ -781,9 +906,49 @@ struct CnnLayout {
   size_t wb_off[NLAYER], n_wb;                    // bf16 weight offsets (elements)
   size_t wt_off[NLAYER], n_wt;                    // bf16 transposed weights (elements)
   // workspace (bytes)
-  size_t x_in, act[NLAYER], head, dz[NLAYER], gpart, bpart, tcount, tvec, tile_loss, ncd, total;
+  size_t x_in, act[NLAYER], head, dz[NLAYER], gpart[NLAYER], tcount, tvec, tile_loss, ncd, total;
   int TX, TY, n_tiles;
+  GwArgs gw;  // the grad-weight plan (no pointers)
 };
+
+// Grad-weight plan.  Layers 1 .. 4: the fewest tiles per workgroup that give at
+// most 256 workgroups (what is resident at once).  Layer 0: GW0_WGS workgroups.
+constexpr int GW_WGS = 256, GW0_WGS = 512;
+static void gw_plan(const ConvDims *D, GwArgs *A) {
+  long long units = 0;
+  for (int i = 0; i < NLAYER; ++i) {
+    GwLayer &L = A->L[i];
+    const ConvDims &d = D[i];
+    L = {};
+    L.Hin = d.Hin;
+    L.Win = d.Win;
+    L.Hout = d.Hout;
+    L.Wout = d.Wout;
+    L.Cout = d.Cout;
+    L.CoutS = d.CoutS;
+    L.Kf = d.Kf;
+    L.cols = 9 * d.Cin;
+    L.mt = d.Mpad / 64;
+    L.tiles_x = (d.Wout + 7) / 8;
+    L.n_tiles = L.tiles_x * (i == 0 ? (d.Hout + 15) / 16 : (d.Hout + 7) / 8);
+    if (i > 0) units += 2LL * L.mt * L.n_tiles;
+  }
+  GwLayer &F = A->L[0];
+  F.per = (F.n_tiles + GW0_WGS - 1) / GW0_WGS;
+  F.splits = (F.n_tiles + F.per - 1) / F.per;
+  for (int per = (int)((units + GW_WGS - 1) / GW_WGS);; ++per) {
+    A->nwork = 0;
+    for (int i = 1; i < NLAYER; ++i) {
+      GwLayer &L = A->L[i];
+      L.per = per;
+      L.splits = (L.n_tiles + per - 1) / per;
+      L.work0 = A->nwork;
+      A->nwork += 2 * L.mt * L.splits;
+    }
+    // a single tile per layer makes 10 work items, so this ends
+    if (A->nwork <= GW_WGS) return;
+  }
+}
 
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -839,16 +1004,13 @@ static bool cnn_layout(int H, int W, CnnLayout *C) {
     C->act[i] = (i < NLAYER - 1) ? take((size_t)d.Hout * d.Wout * d.Cout * 2) : 0;
   }
   C->head = take((size_t)HEAD_CH * C->n_tiles * 4);
-  size_t gp = 0, bp = 0;
+  gw_plan(C->L, &C->gw);
   for (int i = 0; i < NLAYER; ++i) {  // dZ of every layer's output, BF16
     const ConvDims &d = C->L[i];
     C->dz[i] = take((size_t)d.Hout * d.Wout * d.CoutS * 2);
-    const GwSplit g = gw_split(d);
-    gp = std::max(gp, (size_t)g.splits * g.tiles * 4096 * 4);
-    bp = std::max(bp, (size_t)g.splits * (d.Mpad / 64) * 64 * 4);
+    const GwLayer &g = C->gw.L[i];
+    C->gpart[i] = take((size_t)g.splits * g.mt * (g.cols + 1) * 64 * 4);
   }
-  C->gpart = take(gp);
-  C->bpart = take(bp);
   C->tcount = take((size_t)C->n_tiles * 4);
   C->tvec = take((size_t)C->n_tiles * NSLOT * NPAR * 4);
   C->tile_loss = take((size_t)C->n_tiles * 2 * 4);
@@ -900,21 +1062,6 @@ static hipError_t launch_conv_bwd_data(ConvArgs a, hipStream_t st) {
   if (wn == 4) hipLaunchKernelGGL(k_conv_bwd_data<4>, g, dim3(256), 0, st, a);
   else if (wn == 2) hipLaunchKernelGGL(k_conv_bwd_data<2>, g, dim3(256), 0, st, a);
   else hipLaunchKernelGGL(k_conv_bwd_data<1>, g, dim3(256), 0, st, a);
-  return hipGetLastError();
-}
-
-// Grad weight: partial tiles (gw_split), then their sum into dw / db.
-static hipError_t launch_conv_bwd_weight(ConvArgs a, float *dw, float *db, hipStream_t st) {
-  const ConvDims &d = a.d;
-  const GwSplit g = gw_split(d);
-  a.ntile_n = g.ntile_n;
-  a.ksplit = g.ksplit;
-  a.nwork = g.splits * g.tiles;
-  const unsigned grid = (unsigned)((a.nwork + 7) / 8 * 8);
-  hipLaunchKernelGGL(k_conv_bwd_weight, dim3(grid), dim3(256), 0, st, a);
-  const dim3 rg((unsigned)(16 * g.tiles + d.Mpad / 64), (unsigned)((g.splits + GW_CHUNK - 1) / GW_CHUNK));
-  hipLaunchKernelGGL(k_gw_reduce, rg, dim3(256), 0, st, d, g.splits, g.ntile_n, a.gpart, a.bpart,
-                     dw, db);
   return hipGetLastError();
 }
 
@@ -1644,21 +1791,31 @@ int gs2d_cnn_backward(int32_t H, int32_t W, const float *master, const uint16_t 
     hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(1024), 0, st, C.n_tiles,
                        at<const float>(ws, C.tile_loss), at<const int>(ws, C.ncd), loss3);
   const uint16_t *wt = wbf16 + C.n_wb;
+  GwArgs gw = C.gw;
+  int cols = 0;
   for (int i = NLAYER - 1; i >= 0; --i) {
     ConvArgs a = {};
     a.d = C.L[i];
     a.x = (i == 0) ? at<const uint16_t>(ws, C.x_in) : at<const uint16_t>(ws, C.act[i - 1]);
     a.dz = at<const uint16_t>(ws, C.dz[i]);
-    a.gpart = at<float>(ws, C.gpart);
-    a.bpart = at<float>(ws, C.bpart);
-    if (launch_conv_bwd_weight(a, grad + C.w_off[i], grad + C.b_off[i], st) != hipSuccess)
-      return GS2D_EHIP;
+    GwLayer &g = gw.L[i];
+    g.x = a.x;
+    g.dz = a.dz;
+    g.part = at<float>(ws, C.gpart[i]);
+    g.dw = grad + C.w_off[i];
+    g.db = grad + C.b_off[i];
+    cols += g.mt * (g.cols + 1);
     if (i > 0) {
       a.wt = wt + C.wt_off[i];
       a.dz_prev = at<uint16_t>(ws, C.dz[i - 1]);
       if (launch_conv_bwd_data(a, st) != hipSuccess) return GS2D_EHIP;
     }
   }
+  hipLaunchKernelGGL(k_conv_bwd_weight, dim3((unsigned)((gw.nwork + 7) / 8 * 8)), dim3(512), 0, st,
+                     gw);
+  hipLaunchKernelGGL(k_conv_bwd_weight_first, dim3((unsigned)gw.L[0].splits), dim3(256), 0, st,
+                     gw.L[0]);
+  hipLaunchKernelGGL(k_gw_reduce, dim3((unsigned)cols), dim3(256), 0, st, gw);
   return hipGetLastError() == hipSuccess ? GS2D_OK : GS2D_EHIP;
 }
 

@@ -433,7 +433,8 @@ def test_cnn_adam_matches_oracle_decoupled_decay():
 
 
 # layer 0 in tiles of 32 x 4 outputs, the others of 8 x 8: filled exactly, one
-# row and column more, one less
-@pytest.mark.parametrize("hw", [(64, 64), (66, 130), (60, 124)])
+# row and column more, one less; a frame where a grad-weight workgroup walks
+# over five tiles
+@pytest.mark.parametrize("hw", [(64, 64), (66, 130), (60, 124), (520, 600)])
 def test_layers_at_tile_edges(hw):
     test_layers_elementwise_against_oracle(hw)

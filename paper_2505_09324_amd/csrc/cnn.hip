@@ -8,11 +8,10 @@
 // weights BF16 copies of FP32 master weights, accumulation FP32 on MFMA
 // (v_mfma_f32_16x16x32_bf16).
 //
-// Every convolution pass is an implicit GEMM C[M x N] = A[M x K] B[K x N].
-// The forward pass reads its input from a patch of pixels in LDS; the backward
-// passes stage operand tiles in LDS as [row][k] (k contiguous, row pitch padded
-// so that the 16-byte reads of one MFMA step hit distinct banks).  What comes
-// next is loaded into registers while the current tile is multiplied:
+// Every convolution pass is an implicit GEMM C[M x N] = A[M x K] B[K x N] over
+// tiles of pixels; a tile's patch of its input is in LDS (pixel pitch padded so
+// that the reads of one MFMA step spread over the banks), the weights are in
+// registers, and the next tile's patch is loaded while one is multiplied:
 //   forward      M = Cout, N = output pixels, K = (tap, Cin)
 //                A = W[co][tap][ci], B = the tap's input pixels; bias, ReLU
 //                and the BF16 rounding run in the epilogue
@@ -20,9 +19,10 @@
 //                K = (the class's taps, Cout).  With stride 2 an input pixel
 //                (y, x) receives output gradients only through the taps
 //                with ty = y + 1 (mod 2) and tx = x + 1 (mod 2): 1, 2, 2 or 4
-//                of the 9, so the four parity classes are separate GEMMs and
-//                no multiply-by-zero is issued.  The epilogue applies the
-//                previous layer's ReLU' and writes its BF16 dZ directly.
+//                of the 9, so the four parity classes are separate GEMMs over
+//                the same pixels of dZ and no multiply-by-zero is issued.  The
+//                epilogue applies the previous layer's ReLU' and writes its
+//                BF16 dZ directly.
 //   grad weight  M = Cout, N = (tap, Cin), K = output pixels, split over
 //                workgroups whose partials a second kernel sums (plain stores:
 //                FP32 atomics from every workgroup cost more than the GEMM).
@@ -45,14 +45,12 @@ constexpr int NLAYER = 5;
 constexpr int HEAD_CH = 73;
 constexpr int NSLOT = 8, NPAR = 8;
 constexpr int KPAD = 32;     // K of the weight matrices is padded to one MFMA step
-constexpr int KS = 64;       // k per LDS stage (grad input)
-constexpr int LP = KS + 8;   // pitch in halves of its rows and of a pixel (144 B = 9 x 16 B)
+constexpr int LP = 64 + 8;   // LDS pitch of a pixel in halves (144 B = 9 x 16 B)
 
 __device__ inline uint16_t f2bf(float x) {  // round to nearest even
   const uint32_t u = __float_as_uint(x);
   return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
-__device__ inline float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 struct ConvDims {
   int Hin, Win, Cin, Hout, Wout, Cout, stride, relu;
@@ -72,32 +70,7 @@ struct ConvArgs {
   float *y_planar;       // forward output [Cout][Hout*Wout] fp32 (head)
   const uint16_t *dz;    // dZ of this layer [Hout*Wout][CoutS] bf16
   uint16_t *dz_prev;     // grad input: dZ of the previous layer [Hin*Win][Cin] bf16
-  int ncls;              // grad input: parity classes (4 for stride 2, else 1)
-  int cls_tile0[5];      // grad input: first workgroup of each class, then the total
 };
-
-// One 32-deep MFMA step of a wave's (16 MI) x (16 NJ) tile.  As / Bs point at
-// the wave's first A / B row in LDS ([row][k] with pitch PITCH); lane l reads
-// row l & 15 of every 16-row block at k + 8 (l >> 4) as one 16-byte load.
-template <int MI, int NJ, int PITCH>
-__device__ __forceinline__ void mfma_step(const uint16_t *As, const uint16_t *Bs, int k, int lane,
-                                          floatx4 (&acc)[MI][NJ]) {
-  const int r = lane & 15, kk = k + (lane >> 4) * 8;
-  bf16x8 av[MI], bv[NJ];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-    av[i] = __builtin_bit_cast(bf16x8,
-                               *reinterpret_cast<const uint4 *>(As + (16 * i + r) * PITCH + kk));
-#pragma unroll
-  for (int j = 0; j < NJ; ++j)
-    bv[j] = __builtin_bit_cast(bf16x8,
-                               *reinterpret_cast<const uint4 *>(Bs + (16 * j + r) * PITCH + kk));
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
-}
 
 // --------------------------------------------------------------- forward --
 // Bias, ReLU and rounding of a wave's 16 x 16 block: lane holds rows row ..
@@ -307,147 +280,179 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(ConvArgs a, int tiles_x, in
 }
 
 // ------------------------------------------------------------ grad input --
-// Parity class c of a stride-2 layer: (py, px) = pixel parities, in order of
-// decreasing K: (1,1) 4 taps, (1,0) 2, (0,1) 2, (0,0) 1.  Stride 1: one class
-// with all 9 taps.  Class pixel (yy, xx) is input pixel (s yy + py, s xx + px);
-// its j-th tap is (ty, tx) with ty = py ? 2 jy : 1 (stride 2) or jy (stride 1).
-struct ParityClass {
-  int py, px, nty, ntx, Hc, Wc;
-};
-__device__ __forceinline__ ParityClass parity_class(const ConvDims &d, int c) {
-  ParityClass k;
-  if (d.stride == 1) {
-    k.py = k.px = 0;
-    k.nty = k.ntx = 3;
-    k.Hc = d.Hin;
-    k.Wc = d.Win;
-  } else {
-    k.py = (c < 2) ? 1 : 0;
-    k.px = (c == 0 || c == 2) ? 1 : 0;
-    k.nty = k.py ? 2 : 1;
-    k.ntx = k.px ? 2 : 1;
-    k.Hc = (d.Hin - k.py + 1) / 2;
-    k.Wc = (d.Win - k.px + 1) / 2;
-  }
-  return k;
+// Two BF16 values of `o` where those of `m` are > 0, else 0.
+__device__ __forceinline__ uint32_t relu_mask(uint32_t o, uint32_t m) {
+  return (__uint_as_float(m << 16) > 0.f ? o & 0xFFFFu : 0u) |
+         (__uint_as_float(m & 0xFFFF0000u) > 0.f ? o & 0xFFFF0000u : 0u);
 }
 
-// Workgroup tile 64 (Cin) x 32 WN (class pixels), staging as the forward.
-template <int WN>
-__global__ void __launch_bounds__(256) k_conv_bwd_data(ConvArgs a) {
-  constexpr int BN = 32 * WN;
-  __shared__ __attribute__((aligned(16))) uint16_t As[64 * LP];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[BN * LP];
+// Stride 2.  A workgroup walks over tiles of 8 x 8 pixels of dZ and forms the 16
+// x 16 input pixels (8 x 8 of each parity class) whose gradients come from
+// those and the next row and column: the 9 x 9 patch of dZ is in LDS, the
+// weights in registers (16 rows x 576 per wave).  A wave reads a shifted pixel
+// block once for all the taps that use it, 8 reads for 18 MFMAs.  The result
+// goes through LDS so that masks are read and pixels written whole.  HBM bound:
+// 31 us for the 149 MB of the second layer's at 1920 x 1080, 12 and 7 us for
+// the next two.  As a GEMM per parity class, whose staging spent 44 us on
+// addresses alone, they took 58, 19 and 9 us.  Three workgroups per compute
+// unit instead of two spill registers: 36, 14 and 9 us.
+constexpr int BT_W = 9;
+__global__ void __launch_bounds__(256, 2) k_conv_bwd_data(ConvArgs a, int tiles_x, int n_tiles) {
+  constexpr int N = BT_W * BT_W * 8, PER = (N + 255) / 256;
+  __shared__ __attribute__((aligned(16))) uint16_t patch[BT_W * BT_W * LP];
+  __shared__ __attribute__((aligned(16))) uint16_t out[256 * LP];
   const ConvDims &d = a.d;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  int c = 0;
-  while (c + 1 < a.ncls && (int)blockIdx.x >= a.cls_tile0[c + 1]) ++c;
-  const ParityClass pc = parity_class(d, c);
-  const long long Pc = (long long)pc.Hc * pc.Wc;
-  const long long n0 = (long long)(blockIdx.x - a.cls_tile0[c]) * BN;
-  const int m0 = blockIdx.y * 64;
-  const int K = pc.nty * pc.ntx * d.CoutS;
-  const int ar = tid >> 2, ak = (tid & 3) * 8;
-  const bool arow_ok = m0 + ar < d.Cin;
-  const uint16_t *wrow = a.wt + (size_t)(arow_ok ? m0 + ar : 0) * d.Kb;
-  const int br = tid >> 3, bk = (tid & 7) * 8;
-  int yb[WN], xb[WN];
-  bool pv[WN];
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, kg = lane >> 4;
+  uint4 v[PER];
+  auto load = [&](int t) {
+    const int oy0 = t / tiles_x * 8, ox0 = t % tiles_x * 8;
 #pragma unroll
-  for (int j = 0; j < WN; ++j) {
-    const long long q = n0 + br + 32 * j;
-    pv[j] = q < Pc;
-    const int yy = pv[j] ? (int)(q / pc.Wc) : 0, xx = pv[j] ? (int)(q - (long long)yy * pc.Wc) : 0;
-    yb[j] = yy * d.stride + pc.py + 1;  // y + 1
-    xb[j] = xx * d.stride + pc.px + 1;
-  }
-  auto tap_of = [&](int jt, int &ty, int &tx) {
-    const int jy = jt / pc.ntx, jx = jt - jy * pc.ntx;
-    ty = (d.stride == 1) ? jy : (pc.py ? 2 * jy : 1);
-    tx = (d.stride == 1) ? jx : (pc.px ? 2 * jx : 1);
-  };
-  uint4 ra[2], rb[WN];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int k = k0 + ak + 32 * h;
-      ra[h] = make_uint4(0, 0, 0, 0);
-      if (arow_ok && k < K) {
-        const int jt = k / d.CoutS, co = k - jt * d.CoutS;
-        int ty, tx;
-        tap_of(jt, ty, tx);
-        ra[h] = *reinterpret_cast<const uint4 *>(wrow + (ty * 3 + tx) * d.CoutS + co);
-      }
-    }
-    const int k = k0 + bk;
-    const int jt = k / d.CoutS, co = k - jt * d.CoutS;
-    int ty, tx;
-    tap_of(jt, ty, tx);
-#pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      rb[j] = make_uint4(0, 0, 0, 0);
-      // output pixel (oy, ox) with s oy = y + 1 - ty (exact by the class choice)
-      const int oy2 = yb[j] - ty, ox2 = xb[j] - tx;
-      if (pv[j] && k < K && oy2 >= 0 && ox2 >= 0) {
-        const int oy = oy2 / d.stride, ox = ox2 / d.stride;
-        if (oy < d.Hout && ox < d.Wout)
-          rb[j] = *reinterpret_cast<const uint4 *>(a.dz + ((size_t)oy * d.Wout + ox) * d.CoutS + co);
-      }
+    for (int j = 0; j < PER; ++j) {
+      const int e = tid + 256 * j, p = e >> 3, py = p / BT_W, px = p - py * BT_W;
+      v[j] = make_uint4(0, 0, 0, 0);
+      if (e < N && oy0 + py < d.Hout && ox0 + px < d.Wout)
+        v[j] = *reinterpret_cast<const uint4 *>(
+            a.dz + ((size_t)(oy0 + py) * d.Wout + ox0 + px) * 64 + 8 * (e & 7));
     }
   };
-  floatx4 acc[2][WN];
+  load(blockIdx.x);
+  uint4 av[18];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int wm = w & 1, wn = w >> 1;
-  load(0);
-  // the epilogue's output pixels and their ReLU masks (the previous layer's
-  // output), fetched now so that the loads overlap the K loop
-  size_t po[WN];
-  uint2 mask[2][WN];
-#pragma unroll
-  for (int j = 0; j < WN; ++j) {
-    const long long q = n0 + 16 * WN * wn + 16 * j + (lane & 15);
-    po[j] = ~(size_t)0;
-    if (q < Pc) {
-      const int yy = (int)(q / pc.Wc), xx = (int)(q - (long long)yy * pc.Wc);
-      po[j] = (size_t)(yy * d.stride + pc.py) * d.Win + (xx * d.stride + pc.px);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int ci = m0 + 32 * wm + 16 * i + 4 * (lane >> 4);
-      mask[i][j] = (po[j] != ~(size_t)0 && ci < d.Cin)
-                       ? *reinterpret_cast<const uint2 *>(a.x + po[j] * d.Cin + ci)
-                       : make_uint2(0, 0);
-    }
-  }
-  for (int k0 = 0; k0 < K; k0 += KS) {
+  for (int k = 0; k < 18; ++k)
+    av[k] = *reinterpret_cast<const uint4 *>(a.wt + (size_t)(16 * w + r) * d.Kb + 32 * k + 8 * kg);
+  for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
     __syncthreads();
-    *reinterpret_cast<uint4 *>(As + ar * LP + ak) = ra[0];
-    *reinterpret_cast<uint4 *>(As + ar * LP + ak + 32) = ra[1];
 #pragma unroll
-    for (int j = 0; j < WN; ++j) *reinterpret_cast<uint4 *>(Bs + (br + 32 * j) * LP + bk) = rb[j];
+    for (int j = 0; j < PER; ++j) {
+      const int e = tid + 256 * j;
+      if (e < N) *reinterpret_cast<uint4 *>(patch + (e >> 3) * LP + 8 * (e & 7)) = v[j];
+    }
     __syncthreads();
-    if (k0 + KS < K) load(k0 + KS);
-    mfma_step<2, WN, LP>(As + 32 * wm * LP, Bs + 16 * WN * wn * LP, 0, lane, acc);
-    if (k0 + 32 < K) mfma_step<2, WN, LP>(As + 32 * wm * LP, Bs + 16 * WN * wn * LP, 32, lane, acc);
-  }
-  // dZ of the previous layer = dL/dx masked by its ReLU' (x > 0), as BF16
+    // thread's part of the output: pixels (row0 + 2 q, x), channels 8 c .. 8 c + 7
+    const int c = tid & 7, x = t % tiles_x * 16 + ((tid >> 3) & 15);
+    const int row0 = t / tiles_x * 16 + (tid >> 7);
+    uint4 mask[8];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int ci = m0 + 32 * wm + 16 * i + 4 * (lane >> 4);
-    if (ci >= d.Cin) continue;
+    for (int q = 0; q < 8; ++q) {
+      mask[q] = make_uint4(0, 0, 0, 0);
+      if (x < d.Win && row0 + 2 * q < d.Hin)
+        mask[q] = *reinterpret_cast<const uint4 *>(
+            a.x + ((size_t)(row0 + 2 * q) * d.Win + x) * 64 + 8 * c);
+    }
+    if (t + (int)gridDim.x < n_tiles) load(t + gridDim.x);
+#pragma unroll 1
+    for (int j = 0; j < 4; ++j) {  // 16 pixels of dZ: rows 2 j and 2 j + 1
+      const uint16_t *base = patch + ((2 * j + (r >> 3)) * BT_W + (r & 7)) * LP + 8 * kg;
+      floatx4 acc[2][2];  // [py][px]
 #pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      if (po[j] == ~(size_t)0) continue;
-      const uint16_t *mb = reinterpret_cast<const uint16_t *>(&mask[i][j]);
-      uint16_t o[4];
+      for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+      // in order of falling shift a class meets its taps in their own order
 #pragma unroll
-      for (int r = 0; r < 4; ++r) o[r] = f2bf(bf2f(mb[r]) > 0.f ? acc[i][j][r] : 0.f);
-      *reinterpret_cast<uint2 *>(a.dz_prev + po[j] * d.Cin + ci) = *reinterpret_cast<uint2 *>(o);
+      for (int sh = 3; sh >= 0; --sh) {
+        const int dy = sh >> 1, dx = sh & 1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const bf16x8 bv = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const uint4 *>(base + (dy * BT_W + dx) * LP + 32 * h));
+#pragma unroll
+          for (int cl = 0; cl < 4; ++cl) {
+            const int py = cl >> 1, px = cl & 1;
+            if (dy > py || dx > px) continue;  // an even row or column has no shifted tap
+            const int ty = py ? (dy ? 0 : 2) : 1, tx = px ? (dx ? 0 : 2) : 1;
+            acc[py][px] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, av[2 * (3 * ty + tx) + h]), bv, acc[py][px], 0, 0, 0);
+          }
+        }
+      }
+#pragma unroll
+      for (int cl = 0; cl < 4; ++cl) {
+        const int py = cl >> 1, px = cl & 1;
+        uint16_t o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = f2bf(acc[py][px][q]);
+        *reinterpret_cast<uint2 *>(
+            out + ((2 * (2 * j + (r >> 3)) + py) * 16 + 2 * (r & 7) + px) * LP + 16 * w + 4 * kg) =
+            *reinterpret_cast<uint2 *>(o);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (x >= d.Win || row0 + 2 * q >= d.Hin) continue;
+      const uint4 o = *reinterpret_cast<const uint4 *>(out + ((tid >> 3) + 32 * q) * LP + 8 * c);
+      *reinterpret_cast<uint4 *>(a.dz_prev + ((size_t)(row0 + 2 * q) * d.Win + x) * 64 + 8 * c) =
+          make_uint4(relu_mask(o.x, mask[q].x), relu_mask(o.y, mask[q].y),
+                     relu_mask(o.z, mask[q].z), relu_mask(o.w, mask[q].w));
     }
   }
+}
+
+// Head (stride 1, 80 stored channels): a workgroup forms 8 x 4 input pixels from
+// the 10 x 6 patch of dZ, 16 channels per wave.  K = (tap, co) runs in steps of
+// 32 across tap borders, so a lane finds the tap of its 8 channels itself.
+// Latency bound (255 workgroups at 1920 x 1080): 5.6 us; staged tap by tap,
+// with 12 waits for memory instead of one, 15 us.
+constexpr int HC = (HEAD_CH + 7) / 8 * 8, HKB = (9 * HC + KPAD - 1) / KPAD * KPAD;
+constexpr int HP = HC + 8;  // LDS pitch of a pixel in halves (176 B = 11 x 16 B)
+__global__ void __launch_bounds__(256) k_conv_bwd_data_head(ConvArgs a, int tiles_x) {
+  constexpr int CH = HC / 8, N = 60 * CH, PER = (N + 255) / 256;
+  __shared__ __attribute__((aligned(16))) uint16_t patch[60 * HP + 8];
+  __shared__ __attribute__((aligned(16))) uint16_t out[32 * LP];
+  const ConvDims &d = a.d;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, kg = lane >> 4;
+  const int y0 = blockIdx.x / tiles_x * 4, x0 = blockIdx.x % tiles_x * 8;
+  uint4 v[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int e = tid + 256 * j, p = e / CH, c = e - p * CH;
+    const int y = y0 - 1 + p / 10, x = x0 - 1 + p % 10;
+    v[j] = make_uint4(0, 0, 0, 0);
+    if (e < N && y >= 0 && y < d.Hout && x >= 0 && x < d.Wout)
+      v[j] = *reinterpret_cast<const uint4 *>(a.dz + ((size_t)y * d.Wout + x) * HC + 8 * c);
+  }
+  uint4 av[HKB / 32];
+#pragma unroll
+  for (int k = 0; k < HKB / 32; ++k)
+    av[k] = *reinterpret_cast<const uint4 *>(a.wt + (size_t)(16 * w + r) * HKB + 32 * k + 8 * kg);
+  const int c = tid & 7, y = y0 + (tid >> 6), x = x0 + ((tid >> 3) & 7);
+  const bool in = y < d.Hin && x < d.Win;
+  const size_t at = ((size_t)y * d.Win + x) * 64 + 8 * c;
+  const uint4 mask = in ? *reinterpret_cast<const uint4 *>(a.x + at) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int e = tid + 256 * j, p = e / CH;
+    if (e < N) *reinterpret_cast<uint4 *>(patch + p * HP + 8 * (e - p * CH)) = v[j];
+  }
+  if (tid == 0) *reinterpret_cast<uint4 *>(patch + 60 * HP) = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+  floatx4 acc[2];
+  acc[0] = acc[1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < HKB / 32; ++k) {
+    const int q = 4 * k + kg, tap = q / CH, co = 8 * (q - tap * CH);
+    const int ty = tap / 3, tx = tap - 3 * ty;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      int o = ((2 * j + (r >> 3) + 2 - ty) * 10 + (r & 7) + 2 - tx) * HP + co;
+      if (tap >= 9) o = 60 * HP;  // the padding of K
+      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          __builtin_bit_cast(bf16x8, av[k]),
+          __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(patch + o)), acc[j], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    uint16_t o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = f2bf(acc[j][q]);
+    *reinterpret_cast<uint2 *>(out + (16 * j + r) * LP + 16 * w + 4 * kg) =
+        *reinterpret_cast<uint2 *>(o);
+  }
+  __syncthreads();
+  if (!in) return;
+  const uint4 o = *reinterpret_cast<const uint4 *>(out + (tid >> 3) * LP + 8 * c);
+  *reinterpret_cast<uint4 *>(a.dz_prev + at) = make_uint4(relu_mask(o.x, mask.x), relu_mask(o.y, mask.y),
+                                                          relu_mask(o.z, mask.z), relu_mask(o.w, mask.w));
 }
 
 // ----------------------------------------------------------- grad weight --
@@ -1019,13 +1024,6 @@ static bool cnn_layout(int H, int W, CnnLayout *C) {
   return true;
 }
 
-// Pixel tile 32 WN: the widest that still gives >= min_blocks workgroups.
-static int pick_wn(long long pixels, int mtiles, long long min_blocks) {
-  for (int wn = 4; wn > 1; wn >>= 1)
-    if ((pixels + 32 * wn - 1) / (32 * wn) * mtiles >= min_blocks) return wn;
-  return 1;
-}
-
 // 512 workgroups of k_conv_fwd are resident (two per compute unit), shared by
 // the M tiles.
 static hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t st) {
@@ -1037,31 +1035,18 @@ static hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Grad input: the parity classes' tiles are concatenated along grid x in
-// the class order of parity_class (largest K first).
-static hipError_t launch_conv_bwd_data(ConvArgs a, hipStream_t st) {
+// Grad input: as many resident workgroups walk over the tiles as in the forward
+// pass; the head has one tile per workgroup.
+static hipError_t launch_conv_bwd_data(const ConvArgs &a, hipStream_t st) {
   const ConvDims &d = a.d;
-  const int mt = (d.Cin + 63) / 64, wn = pick_wn((long long)d.Hin * d.Win, mt, 1000);
-  const long long bn = 32 * wn;
-  a.ncls = d.stride == 2 ? 4 : 1;
-  long long tiles = 0;
-  for (int c = 0; c < a.ncls; ++c) {
-    long long px;
-    if (d.stride == 2) {
-      const int py = c < 2 ? 1 : 0, pxp = (c == 0 || c == 2) ? 1 : 0;
-      px = (long long)((d.Hin - py + 1) / 2) * ((d.Win - pxp + 1) / 2);
-    } else {
-      px = (long long)d.Hin * d.Win;
-    }
-    a.cls_tile0[c] = (int)tiles;
-    tiles += (px + bn - 1) / bn;
+  const int tx = (d.Wout + 7) / 8;
+  if (d.stride == 2) {
+    const int n = tx * ((d.Hout + 7) / 8);
+    hipLaunchKernelGGL(k_conv_bwd_data, dim3((unsigned)std::min(n, 512)), dim3(256), 0, st, a, tx, n);
+  } else {
+    hipLaunchKernelGGL(k_conv_bwd_data_head, dim3((unsigned)(tx * ((d.Hout + 3) / 4))), dim3(256), 0,
+                       st, a, tx);
   }
-  a.cls_tile0[a.ncls] = (int)tiles;
-  if (tiles == 0) return hipSuccess;
-  const dim3 g((unsigned)tiles, (unsigned)mt);
-  if (wn == 4) hipLaunchKernelGGL(k_conv_bwd_data<4>, g, dim3(256), 0, st, a);
-  else if (wn == 2) hipLaunchKernelGGL(k_conv_bwd_data<2>, g, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL(k_conv_bwd_data<1>, g, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -72,6 +72,28 @@ struct ConvArgs {
   uint16_t *dz_prev;     // grad input: dZ of the previous layer [Hin*Win][Cin] bf16
 };
 
+// Tile of this workgroup out of n (or n: none), grid rounded up to eighths.
+// Workgroup b runs on XCD b % 8: each XCD gets a contiguous eighth, so that
+// the lines that neighbouring tiles share are fetched into one L2.
+__device__ __forceinline__ int xcd_tile(int n) {
+  const int t = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  return min(t, n);
+}
+
+// Range-checked loads at base + off, base the same for the whole wave: an
+// offset of OUTSIDE gives zeros.
+typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
+constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (uint32_t)bytes, 0x00020000);
+}
+__device__ __forceinline__ uint4 load16(__amdgpu_buffer_rsrc_t b, uint32_t off, int base) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, base, 0));
+}
+__device__ __forceinline__ float load4(__amdgpu_buffer_rsrc_t b, uint32_t off, int base) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, base, 0));
+}
+
 // --------------------------------------------------------------- forward --
 // Bias, ReLU and rounding of a wave's 16 x 16 block: lane holds rows row ..
 // row + 3 of output pixel `col` (D[4 (lane >> 4) + r][lane & 15]).
@@ -103,8 +125,8 @@ __device__ __forceinline__ void store_fwd(const ConvArgs &a, const floatx4 &acc,
 // multiplies straight from LDS, one tap of one pixel per 16-byte read; waves 2
 // x 2, each 32 channels x 64 pixels with its weights in registers.  The
 // output tile goes through LDS so that whole 128-byte pixels are stored.  HBM
-// bound: 150 MB at 1920 x 1080 (frame, residual, x_in and the output), 39 us.
-// As two launches, a conversion and an implicit GEMM that read x_in back 2.25
+// bound: 150 MB at 1920 x 1080 (frame, residual, x_in and the output), 37 us
+// (47 us with 64-bit addresses and a border test per load).  As two launches, a conversion and an implicit GEMM that read x_in back 2.25
 // times, it took 17 + 37 us; with the output stored from the accumulators (32
 // bytes of a pixel at a time) 57 us.
 constexpr int C0_TW = 32, C0_TH = 4, C0_PW = 2 * C0_TW + 1, C0_PH = 2 * C0_TH + 1;
@@ -119,12 +141,16 @@ k_conv_first(ConvArgs a, const float *__restrict__ frame, const float *__restric
   const ConvDims &d = a.d;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int tiles_x = (d.Wout + C0_TW - 1) / C0_TW;
-  const int ox0 = (blockIdx.x % tiles_x) * C0_TW, oy0 = (blockIdx.x / tiles_x) * C0_TH;
+  const int n_tiles = tiles_x * ((d.Hout + C0_TH - 1) / C0_TH), t = xcd_tile(n_tiles);
+  if (t >= n_tiles) return;
+  const int ox0 = t % tiles_x * C0_TW, oy0 = t / tiles_x * C0_TH;
   const size_t HW = (size_t)d.Hin * d.Win;
   const int wm = w & 1, wn = w >> 1, r = lane & 15, kg = lane >> 4;
   float f[C0_PER][3], q[C0_PER][3];
   size_t at[C0_PER];
   int own[C0_PER];
+  const __amdgpu_buffer_rsrc_t fb = buffer_of(frame, 12 * HW), qb = buffer_of(prev, prev ? 12 * HW : 0);
+  const int plane = (int)(4 * HW);
 #pragma unroll
   for (int j = 0; j < C0_PER; ++j) {
     const int e = tid + 256 * j, py = e / C0_PW, pxx = e - py * C0_PW;
@@ -132,11 +158,12 @@ k_conv_first(ConvArgs a, const float *__restrict__ frame, const float *__restric
     const bool in = e < C0_N && iy >= 0 && iy < d.Hin && ix >= 0 && ix < d.Win;
     at[j] = (size_t)iy * d.Win + ix;
     own[j] = in && py > 0 && pxx > 0;  // the first row and column belong to the tiles before
+    const uint32_t o = in ? (uint32_t)(iy * d.Win + ix) * 4u : OUTSIDE;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      f[j][c] = in ? frame[c * HW + at[j]] : 0.f;
-      q[j][c] = prev ? (in ? prev[c * HW + at[j]] : 0.f) : f[j][c];
-    }
+    for (int c = 0; c < 3; ++c) f[j][c] = load4(fb, o, c * plane);
+    if (prev)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) q[j][c] = load4(qb, o, c * plane);
   }
   uint4 av[3][2];
 #pragma unroll
@@ -467,12 +494,13 @@ __global__ void __launch_bounds__(256) k_conv_bwd_data_head(ConvArgs a, int tile
 // reads x from a zeroed part of LDS instead (0 times infinity would not be 0).
 // The pitches put the 8 pixels that 32 lanes read on distinct banks.
 //
-// HBM and latency bound.  At 1920 x 1080 the 64-channel layers take 40 us (126
-// MB with the partials), the first layer 20 us (100 MB and 9 MB of partials),
-// the sums 14 us.  As GEMMs over 64 x 64 tiles that transposed in registers on
-// their way to LDS, every column tile read dZ again and every tap its pixels
-// of x (300 MB through L2 for the second layer alone): 44, 18, 12 and 13 us,
-// the first layer 40 us, five sums 32 us.
+// HBM and latency bound.  At 1920 x 1080 the 64-channel layers take 36 us (126
+// MB with the partials; 40 us when every load tested for the border), the first
+// layer 20 us (100 MB and 9 MB of partials), the sums 14 us.  As GEMMs over 64
+// x 64 tiles that transposed in registers on their way to LDS, every column
+// tile read dZ again and every tap its pixels of x (300 MB through L2 for the
+// second layer alone): 44, 18, 12 and 13 us, the first layer 40 us, five sums
+// 32 us.
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) short4v lds_short4;
@@ -539,21 +567,35 @@ __device__ __forceinline__ void gw_layer(const GwLayer &L, int work, uint8_t *ld
   struct Stage {
     uint4 x[PER], z;
   };
-  auto load = [&](Stage &v, int t) {
-    const int oy0 = t / L.tiles_x * 8, ox0 = t % L.tiles_x * 8;
+  const __amdgpu_buffer_rsrc_t xs = buffer_of(L.x, (size_t)L.Hin * L.Win * 128);
+  const __amdgpu_buffer_rsrc_t zs = buffer_of(L.dz, (size_t)L.Hout * L.Wout * L.CoutS * 2);
+  uint32_t fx[PER];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int e = tid + 512 * j, p = e >> 2, py = p / PW, px = p - py * PW;
-      const int iy = oy0 * S - 1 + py, ix = ox0 * S - 1 + px;
-      v.x[j] = make_uint4(0, 0, 0, 0);
-      if (e < NX && iy >= 0 && iy < L.Hin && ix >= 0 && ix < L.Win)
-        v.x[j] = *reinterpret_cast<const uint4 *>(L.x + ((size_t)iy * L.Win + ix) * 64 + 32 * half +
-                                                  8 * (e & 3));
+  for (int j = 0; j < PER; ++j) {
+    const int e = tid + 512 * j, p = e >> 2;
+    fx[j] = e < NX ? (uint32_t)(p / PW * L.Win + p % PW) * 128u + 64u * half + 16u * (e & 3) : OUTSIDE;
+  }
+  const int zy = tid >> 6, zx = (tid >> 3) & 7;
+  const uint32_t fz = m0 + 8 * (tid & 7) < L.CoutS
+                          ? (uint32_t)((zy * L.Wout + zx) * L.CoutS + m0 + 8 * (tid & 7)) * 2u
+                          : OUTSIDE;
+  auto load = [&](Stage &v, int t) {
+    const int oy0 = t / L.tiles_x * 8, ox0 = t % L.tiles_x * 8, iy0 = oy0 * S - 1, ix0 = ox0 * S - 1;
+    const int xbase = (iy0 * L.Win + ix0) * 128, zbase = (oy0 * L.Wout + ox0) * L.CoutS * 2;
+    if (iy0 >= 0 && ix0 >= 0 && iy0 + PW <= L.Hin && ix0 + PW <= L.Win) {  // also within dZ
+#pragma unroll
+      for (int j = 0; j < PER; ++j) v.x[j] = load16(xs, fx[j], xbase);
+      v.z = load16(zs, fz, zbase);
+    } else {
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        const int e = tid + 512 * j, p = e >> 2, iy = iy0 + p / PW, ix = ix0 + p % PW;
+        const bool in = e < NX && iy >= 0 && iy < L.Hin && ix >= 0 && ix < L.Win;
+        v.x[j] = load16(xs, in ? fx[j] + xbase : OUTSIDE, 0);
+      }
+      const bool in = fz != OUTSIDE && oy0 + zy < L.Hout && ox0 + zx < L.Wout;
+      v.z = load16(zs, in ? fz + zbase : OUTSIDE, 0);
     }
-    const int p = tid >> 3, oy = oy0 + (p >> 3), ox = ox0 + (p & 7), co = m0 + 8 * (tid & 7);
-    v.z = make_uint4(0, 0, 0, 0);
-    if (oy < L.Hout && ox < L.Wout && co < L.CoutS)
-      v.z = *reinterpret_cast<const uint4 *>(L.dz + ((size_t)oy * L.Wout + ox) * L.CoutS + co);
   };
   auto put = [&](const Stage &v, uint8_t *buf) {
 #pragma unroll
@@ -1023,6 +1065,9 @@ static bool cnn_layout(int H, int W, CnnLayout *C) {
   C->total = o;
   return true;
 }
+
+// Workgroups for n tiles in eighths (xcd_tile).
+static unsigned xcd_grid(int n) { return (unsigned)((n + 7) / 8 * 8); }
 
 // 512 workgroups of k_conv_fwd are resident (two per compute unit), shared by
 // the M tiles.
@@ -1679,8 +1724,8 @@ int gs2d_cnn_forward(int32_t H, int32_t W, const float *frame, const float *prev
     if (i == 0) {
       const ConvDims &d = a.d;
       hipLaunchKernelGGL(k_conv_first,
-                         dim3((unsigned)((d.Wout + C0_TW - 1) / C0_TW) *
-                              (unsigned)((d.Hout + C0_TH - 1) / C0_TH)),
+                         dim3(xcd_grid((d.Wout + C0_TW - 1) / C0_TW *
+                                       ((d.Hout + C0_TH - 1) / C0_TH))),
                          dim3(256), 0, st, a, frame, prev, x);
     } else if (launch_conv_fwd(a, st) != hipSuccess) {
       return GS2D_EHIP;

@@ -364,6 +364,125 @@ __device__ inline void exchange_sums(float *xch, float (&acc)[PPL][3]) {
   }
 }
 
+// dL/dC of lane N of this lane's row of 16 (g, as DPP operands): its product
+// with the colour B.yzw, and its share `wgt` added to the sums c.  s_nop: a
+// register that a DPP operand reads must be two states old.
+template <int N>
+__device__ __forceinline__ float row_pixel(const float (&g)[3], const float4 &B, float wgt, float *c) {
+  float d;
+  asm("s_nop 1\n"
+      "v_mul_f32_dpp %0, %4, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f32_dpp %0, %5, %8 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f32_dpp %0, %6, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f32_dpp %1, %4, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f32_dpp %2, %5, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f32_dpp %3, %6, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf"
+      : "=&v"(d), "+v"(c[0]), "+v"(c[1]), "+v"(c[2])
+      : "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(B.y), "v"(B.z), "v"(B.w), "v"(wgt), "n"(N));
+  return d;
+}
+
+// bwd_batch's state over the pixel columns: v[0..4] as bwd_chunk's vals before
+// the factors 1/l1 (0, 2) and 1/l3 (4), v[5..7] the colours.
+struct BatchSums {
+  float v[8];
+  bool any;
+};
+template <int PPL, bool CHECK_HITS, int N>
+__device__ __forceinline__ void batch_pixels(BatchSums &T, float &t0, float &t2, const float4 &B,
+                                             float u1s, float base, const float (&g)[PPL][3]) {
+  float u2 = base * B.x;  // the next pixel row adds 1/l3
+#pragma unroll
+  for (int r = 0; r < PPL; ++r, u2 += B.x) {
+    const float q = u1s + u2 * u2;
+    const float e = __builtin_amdgcn_exp2f(-q);
+    const bool in_cut = q <= CUTOFF_QS;
+    const float wgt = in_cut ? e : 0.f;
+    if (CHECK_HITS) T.any |= in_cut;
+    const float sn = row_pixel<N>(g[r], B, wgt, T.v + 5) * wgt;
+    const float s2 = sn * u2;
+    t0 += sn;
+    t2 += s2;
+    T.v[4] += s2 * u2;
+  }
+}
+template <int PPL, bool CHECK_HITS, int COL>
+__device__ __forceinline__ void batch_column(BatchSums &T, const float4 &A, const float4 &B, bool live,
+                                             float x0, const float (&yb)[2], const float (&g)[PPL][3]) {
+  const float u1 = ((x0 + (float)COL) - A.x) * A.z;
+  const float u1s = live ? u1 * u1 : INFINITY;
+  float t0 = 0.f, t2 = 0.f;
+  batch_pixels<PPL, CHECK_HITS, COL>(T, t0, t2, B, u1s, yb[0] - A.w * u1, g);
+  batch_pixels<PPL, CHECK_HITS, COL + 8>(T, t0, t2, B, u1s, yb[1] - A.w * u1, g);
+  t2 *= B.x;
+  const float s1 = u1 * t0 - A.w * t2;
+  T.v[0] += s1;
+  T.v[1] += t2;
+  T.v[2] += s1 * u1;
+  T.v[3] += t2 * u1;
+  if constexpr (COL < 7) batch_column<PPL, CHECK_HITS, COL + 1>(T, A, B, live, x0, yb, g);
+}
+
+// Backward of up to 16 Gaussians at once, entries [k0, min(k0 + 16, end)): lane
+// L takes Gaussian L & 15 over the pixels of its row of 16 lanes, whose dL/dC
+// reach it as DPP operands, and sums in registers.  The raster is bound by
+// vector instructions (about 85 % of the issue slots at 1920 x 1080).  One
+// Gaussian at a time, 18 of its 67 for 128 pixels reduce 8 sums over 64 lanes
+// and 12 more set it up; here 16 Gaussians share 12 for the reduction over 4
+// rows, a pixel column's terms are formed once for its pixels, and no LDS is
+// read for dL/dC (with lanes fetching it by ds_bpermute, 8 Gaussians at a time,
+// the LDS became the bound and nothing was gained).  1920x1080 / 30,000, 20
+// iterations 1296 -> 1146 us, 12 mixed frames, 10 iterations 2858 -> 2468 us.
+template <class C, int PPL, bool CHECK_HITS>
+__device__ __forceinline__ void bwd_batch(const Smem<C> &S, float *acc, int k0, int end, float pxc,
+                                          float pyc0, const float (&g)[PPL][3]) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int k = k0 + (lane & 15);
+  const bool live = k < end;
+  const int j = S.list[w][min(k, end - 1)];
+  const float4 A = S.A[j], B = S.B[j];
+  const float x0 = pxc - (float)(lane & 7);
+  const float y0 = pyc0 - (float)(((lane >> 3) & 1) * PPL);  // the row's first pixel row
+  const float yb[2] = {y0 - A.y, (y0 + (float)PPL) - A.y};
+  BatchSums T = {};
+  batch_column<PPL, CHECK_HITS, 0>(T, A, B, live, x0, yb, g);
+  T.v[0] *= A.z;
+  T.v[2] *= A.z;
+  T.v[4] *= B.x;
+  // the four rows' sums: each exchange halves the values a lane carries
+  float b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(T.v[i]), __float_as_uint(T.v[i + 4]),
+                                              false, false);
+    b[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[i]), __float_as_uint(b[i + 2]),
+                                              false, false);
+    c[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  bool add = live;
+  if (CHECK_HITS) {
+    const unsigned long long m = __ballot(T.any);
+    add = add && (((m | m >> 16 | m >> 32 | m >> 48) >> (lane & 15)) & 1);
+  }
+  if (add) {
+    float *dst = acc + j * 8 + (lane >> 5) * 4 + ((lane >> 4) & 1) * 2;
+    atomicAdd(dst, c[0]);
+    atomicAdd(dst + 1, c[1]);
+  }
+}
+
+// Gaussians from which a batch is faster than one at a time: 16 take about 645
+// vector instructions at 2 pixels per lane, one by itself 67 (us per 20
+// iterations at 1920x1080 / 30,000, from 8: 1146, from 10: 1151, full batches
+// only: 1200, never: 1296).  Where four wavefronts share a list they split it
+// finer than that (640x360 / 1000, 50 iterations: 962 without, 989 with); two
+// gain (960x540 / 7000: 645 without, 607 with).
+constexpr int BATCH_MIN = 8;
+
 // Backward over entries [beg, end) of this wavefront's list of a staged,
 // compacted chunk; adds into acc[CH][8] in LDS.
 // CHECK_HITS skips (uniformly per wavefront) Gaussians with no pixel inside
@@ -372,7 +491,11 @@ template <class C, int PPL, bool CHECK_HITS>
 __device__ inline void bwd_chunk(const Smem<C> &S, float *acc, int beg, int end, float pxc,
                                  float pyc0, const float (&g)[PPL][3]) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int k = beg; k < end; ++k) {
+  int k = beg;
+  if constexpr (C::NW <= 2 * C::NB)
+    for (; end - k >= BATCH_MIN; k += 16)
+      bwd_batch<C, PPL, CHECK_HITS>(S, acc, k, end, pxc, pyc0, g);
+  for (; k < end; ++k) {
     const int j = S.list[w][k];
     const float4 A = S.A[j], B = S.B[j];
     const float u1 = (pxc - A.x) * A.z;
@@ -532,45 +655,32 @@ __device__ inline void fused_tile(Smem<C> &S, float *acc, float *xch, const Fram
   float g[PPL][3];
   float l;
   int kb, ke;
-  if (end - beg <= C::CH) {
-    const int cnt = end - beg;
-    if constexpr (!ONE) __syncthreads();  // LDS of a previous tile (persistent callers) is free
-    stage_chunk<C, TILE, EXACT>(S, f.keys, beg, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active,
-                                part);
-    for (int i = threadIdx.x; i < cnt * 8; i += C::NT) acc[i] = 0.f;
+  const bool once = end - beg <= C::CH;  // the whole list fits one chunk
+  int len = 0;
+  for (int c = beg; c < end; c += C::CH) {
+    const int cnt = min(C::CH, end - c);
+    if (!ONE || c != beg) __syncthreads();  // LDS of a previous tile or chunk is free
+    stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active, part);
+    if (once)
+      for (int i = threadIdx.x; i < cnt * 8; i += C::NT) acc[i] = 0.f;
     __syncthreads();
-    int len = compact_chunk<C>(S, cnt);
+    len = compact_chunk<C>(S, cnt);
     list_run<C>(len, &kb, &ke);
     const int kept = fwd_chunk<C, PPL, !EXACT>(S, kb, ke, pxc, pyc0, inside, a);
     if constexpr (!EXACT) len = kept;
-    exchange_sums<C, PPL>(xch, a);
-    residuals<TILE, PPL>(a, tg, inside, grad_scale, g, &l);
-    if (w < C::NB) wave_loss(l, loss_slots + part * C::NB + w);
-    if (f.active) len = keep_active<C>(S, len);
-    list_run<C>(len, &kb, &ke);
-    bwd_chunk<C, PPL, false>(S, acc, kb, ke, pxc, pyc0, g);
-    __syncthreads();
-    flush_grads<C, ONE>(S, acc, cnt, g_xy, g_chol, g_rgb);
-    return;
-  }
-  for (int c = beg; c < end; c += C::CH) {
-    const int cnt = min(C::CH, end - c);
-    __syncthreads();
-    stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, nullptr, part);
-    __syncthreads();
-    list_run<C>(compact_chunk<C>(S, cnt), &kb, &ke);
-    fwd_chunk<C, PPL, false>(S, kb, ke, pxc, pyc0, inside, a);
   }
   exchange_sums<C, PPL>(xch, a);
   residuals<TILE, PPL>(a, tg, inside, grad_scale, g, &l);
   if (w < C::NB) wave_loss(l, loss_slots + part * C::NB + w);
   for (int c = beg; c < end; c += C::CH) {
     const int cnt = min(C::CH, end - c);
-    __syncthreads();
-    stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active, part);
-    for (int i = threadIdx.x; i < cnt * 8; i += C::NT) acc[i] = 0.f;
-    __syncthreads();
-    int len = compact_chunk<C>(S, cnt);
+    if (!once) {
+      __syncthreads();
+      stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active, part);
+      for (int i = threadIdx.x; i < cnt * 8; i += C::NT) acc[i] = 0.f;
+      __syncthreads();
+      len = compact_chunk<C>(S, cnt);
+    }
     if (f.active) len = keep_active<C>(S, len);
     list_run<C>(len, &kb, &ke);
     bwd_chunk<C, PPL, !EXACT>(S, acc, kb, ke, pxc, pyc0, g);

@@ -85,6 +85,24 @@ def test_backward_tiny_frame(T, ppl):
     assert_grads_close({"xy": host(gx), "chol": host(gc), "rgb": host(gr)}, ref)
 
 
+# every sub-block's list is the whole frame's: one at a time, a batch of 16
+# with lanes to spare, full, and full with a rest
+@pytest.mark.parametrize("T,ppl", VARIANTS)
+@pytest.mark.parametrize("N", [1, 7, 8, 15, 16, 17, 24, 41])
+def test_backward_list_lengths(N, T, ppl):
+    print(f"bwd lists of {N} T={T} ppl={ppl}", flush=True)
+    W, H = 30, 35
+    xy, chol, rgb = synth.random_gaussians(N, W, H, seed=60 + N, scale_lo=20.0, scale_hi=30.0)
+    chol[:, 1] = np.random.default_rng(N).uniform(-5, 5, N).astype(np.float32)
+    rgb -= 0.5
+    dl = np.random.default_rng(61).standard_normal((3, H, W)).astype(np.float32)
+    f = GpuFrame(W, H, N, T, ppl=ppl)
+    f.bin(dev(xy), dev(chol))
+    gx, gc, gr = f.backward(dev(rgb), dev(dl))
+    ref = gradients(xy, chol, rgb, dl, H, W)
+    assert_grads_close({"xy": host(gx), "chol": host(gc), "rgb": host(gr)}, ref)
+
+
 def test_backward_long_lists():
     print("bwd long lists", flush=True)
     W, H, N = 64, 48, 1200

@@ -127,36 +127,25 @@ struct FrameArgs {
   int *tick;
 };
 
-// Whether the ellipse q' <= qmax (staged units: u1 = dx a, u2 = (dy - l2s u1)
-// r3s) reaches the rectangle [X0, X1] x [Y0, Y1].  q' is a convex quadratic,
-// so outside its centre its minimum over the rectangle lies on an edge that
-// faces the centre: on the edge x = Xe the minimum sits where u2 = 0 (dy =
-// l2s u1), clamped to the edge; on the edge y = Ye, q' = (a dx)^2 +
-// (e - c dx)^2 with c = l2s a r3s and e = dy r3s, minimised at dx = c e /
-// (a^2 + c^2), clamped.  A NaN anywhere counts as a hit.
-__device__ inline bool ellipse_meets_rect(float mx, float my, float a, float l2s, float r3s,
-                                          float X0, float X1, float Y0, float Y1, float qmax) {
-  const bool left = mx < X0, right = mx > X1, below = my < Y0, above = my > Y1;
-  if (!(left || right || below || above)) return true;
-  float best = INFINITY;
-  if (left || right) {
-    const float u1 = ((left ? X0 : X1) - mx) * a;
-    const float t = l2s * u1;
-    const float dy = fminf(fmaxf(t, Y0 - my), Y1 - my);
-    const float u2 = (dy - t) * r3s;
-    best = u1 * u1 + u2 * u2;
-  }
-  if (below || above) {
-    const float dy = (below ? Y0 : Y1) - my;
-    const float c = l2s * a * r3s, e = dy * r3s;
-    // an approximate reciprocal only moves the evaluated point off the
-    // minimiser, which raises q' by a second-order amount
-    const float dx = fminf(fmaxf(c * e * __builtin_amdgcn_rcpf(a * a + c * c), X0 - mx), X1 - mx);
-    const float u1 = dx * a;
-    const float u2 = (dy - l2s * u1) * r3s;
-    best = fminf(best, u1 * u1 + u2 * u2);
-  }
-  return !(best > qmax);
+// The ellipse q' <= qmax (staged units: u1 = dx a, u2 = dy r3s - c u1 with c =
+// l2s r3s), cut by the strip of rows d0 <= dy <= d1: true unless it misses the
+// strip, and then the least and largest u1 of the cut.  sq = sqrt(qmax).  The
+// rightmost point is (sq, l2s sq); where that lies outside the strip, the cut
+// ends on the strip's nearer edge e = dy r3s, at a root of (1 + c^2) u1^2 - 2
+// c e u1 + e^2 = qmax.  A NaN anywhere comes out as a NaN range.  The cut is
+// convex, so it meets the sub-blocks of the strip whose columns its range
+// meets: 57 vector instructions per row of sub-blocks, where a test per
+// sub-block took 42 each (1920x1080 / 30,000, 20 iterations, with the loss sum
+// in DPP adds: 1154 -> 1133 us; 4 pixels per lane 1422 -> 1367 us).
+__device__ inline bool ellipse_in_strip(float l2s, float r3s, float d0, float d1, float qmax,
+                                        float sq, float *lo, float *hi) {
+  const float c = l2s * r3s, k = 1.f + c * c, ik = __builtin_amdgcn_rcpf(k), t = l2s * sq;
+  const float er = (t < d0 ? d0 : d1) * r3s, el = (-t < d0 ? d0 : d1) * r3s;
+  const float sr = qmax * k - er * er, sl = qmax * k - el * el;
+  const bool in_r = t >= d0 && t <= d1, in_l = -t >= d0 && -t <= d1;
+  *hi = in_r ? sq : (c * er + __builtin_amdgcn_sqrtf(sr)) * ik;
+  *lo = in_l ? -sq : (c * el - __builtin_amdgcn_sqrtf(sl)) * ik;
+  return !((!in_r && sr < 0.f) || (!in_l && sl < 0.f));
 }
 
 // Stage keys[beg, beg+cnt) into LDS with their sub-block masks: bit w is set
@@ -206,16 +195,26 @@ __device__ inline void stage_chunk(Smem<C> &S, const uint32_t *__restrict__ keys
     const int by0 = (int)fmaxf(by0f, (float)sy0), by1 = (int)fminf(by1f, (float)sy1);
     const float qmax = CUTOFF_QS + 0.01f * (1.0f + fabsf(l2s * r3s));
     uint32_t m = 0;
-    for (int by = by0; by <= by1; ++by) {
-      const float Y0 = (float)(ty * TILE + by * C::SBH) + 0.5f;
-      const float Y1 = fminf(Y0 + (float)(C::SBH - 1), ylast);
-      for (int bx = bx0; bx <= bx1; ++bx) {
-        const float X0 = (float)(tx * TILE + bx * 8) + 0.5f;
-        const float X1 = fminf(X0 + 7.0f, xlast);
-        if (!EXACT ||
-            (X0 <= X1 && Y0 <= Y1 && ellipse_meets_rect(g0.x, g0.y, a, l2s, r3s, X0, X1, Y0, Y1, qmax)))
-          m |= 1u << (by * C::SBX + bx - sb0);
+    if constexpr (EXACT) {
+      const float sq = __builtin_amdgcn_sqrtf(qmax), ia = __builtin_amdgcn_rcpf(a);
+      // the centre and the last pixel column, from the tile's first
+      const float left = g0.x - ((float)(tx * TILE) + 0.5f), xl = xlast - ((float)(tx * TILE) + 0.5f);
+      for (int by = by0; by <= by1; ++by) {
+        const float Y0 = (float)(ty * TILE + by * C::SBH) + 0.5f;
+        const float Y1 = fminf(Y0 + (float)(C::SBH - 1), ylast);
+        float u0, u1;
+        if (Y0 > Y1 || !ellipse_in_strip(l2s, r3s, Y0 - g0.y, Y1 - g0.y, qmax, sq, &u0, &u1)) continue;
+        // columns from the first whose last pixel is not left of the cut, to
+        // the last whose first is not right of it; the box's after a NaN
+        const bool cut = u0 <= u1;
+        const float x0 = left + fminf(u0 * ia, u1 * ia), x1 = left + fmaxf(u0 * ia, u1 * ia);
+        const int c0 = cut ? (int)fmaxf(ceilf((x0 - 7.f) * inv_w), (float)bx0) : bx0;
+        const int c1 = cut ? (int)fminf(floorf(fminf(x1, xl) * inv_w), (float)bx1) : bx1;
+        if (c0 <= c1 && !(x0 > xl)) m |= ((2u << (c1 - c0)) - 1u) << (by * C::SBX + c0 - sb0);
       }
+    } else {
+      for (int by = by0; by <= by1; ++by)
+        for (int bx = bx0; bx <= bx1; ++bx) m |= 1u << (by * C::SBX + bx - sb0);
     }
     S.mask[j] = (uint16_t)m;
   }
@@ -578,8 +577,20 @@ __device__ inline void flush_grads(const Smem<C> &S, const float *acc, int cnt,
 // partials are kept per wavefront (tile t, wavefront w at t * NW + w), so a
 // wavefront never waits for the rest of its tile to record its loss.
 __device__ inline void wave_loss(float v, float *__restrict__ slot) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  if ((threadIdx.x & 63) == 0) *slot = v;
+  v += dpp<DPP_QUAD_XOR1>(v);
+  v += dpp<DPP_QUAD_XOR2>(v);
+  v += dpp<DPP_ROW_HALF_MIRROR>(v);
+  v += dpp<DPP_ROW_ROR8>(v);
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  if ((threadIdx.x & 63) == 0) *slot = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// base[i] with a 32-bit byte offset beside a uniform base (a frame has at most
+// 65536 tiles, so its planes stay below 2^28 bytes; Gaussians below 2^16).
+__device__ __forceinline__ float at_index(const float *base, uint32_t i) {
+  return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + 4u * i);
 }
 
 // Bit r set: pixel row r of this lane lies inside the frame.
@@ -646,10 +657,10 @@ __device__ inline void fused_tile(Smem<C> &S, float *acc, float *xch, const Fram
   float tg[PPL][3];
 #pragma unroll
   for (int r = 0; r < PPL; ++r) {
-    const size_t p = ((inside >> r) & 1u) ? (size_t)(py0 + r) * f.W + px : 0;
-    tg[r][0] = target[p];
-    tg[r][1] = target[HW + p];
-    tg[r][2] = target[2 * HW + p];
+    const uint32_t p = ((inside >> r) & 1u) ? (uint32_t)((py0 + r) * f.W + px) : 0;
+    tg[r][0] = at_index(target, p);
+    tg[r][1] = at_index(target + HW, p);
+    tg[r][2] = at_index(target + 2 * HW, p);
   }
   float a[PPL][3] = {};
   float g[PPL][3];

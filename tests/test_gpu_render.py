@@ -85,6 +85,22 @@ def test_backward_tiny_frame(T, ppl):
     assert_grads_close({"xy": host(gx), "chol": host(gc), "rgb": host(gr)}, ref)
 
 
+@pytest.mark.parametrize("T,ppl", VARIANTS)
+def test_forward_needles(T, ppl):
+    """Thin, sheared ellipses of every sign: the sub-blocks that a row strip's
+    cut of the ellipse selects hold every pixel inside the cutoff."""
+    print(f"fwd needles T={T} ppl={ppl}", flush=True)
+    W, H, N = 75, 67, 120
+    r = np.random.default_rng(63)
+    xy = (r.uniform(-0.1, 1.1, (N, 2)) * (W, H)).astype(np.float32)
+    sign = r.choice([-1.0, 1.0], (N, 2))
+    chol = np.stack([sign[:, 0] * r.uniform(0.3, 12, N), r.uniform(-12, 12, N),
+                     sign[:, 1] * r.uniform(0.3, 2, N)], 1).astype(np.float32)
+    rgb = r.uniform(-1, 1, (N, 3)).astype(np.float32)
+    img, _, _ = GpuFrame(W, H, N, T, ppl=ppl).forward(dev(xy), dev(chol), dev(rgb))
+    assert_pixels_close(host(img), render_box(xy, chol, rgb, H, W))
+
+
 # every sub-block's list is the whole frame's: one at a time, a batch of 16
 # with lanes to spare, full, and full with a rest
 @pytest.mark.parametrize("T,ppl", VARIANTS)

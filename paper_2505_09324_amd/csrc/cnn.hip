@@ -119,16 +119,17 @@ __device__ __forceinline__ void store_fwd(const ConvArgs &a, const floatx4 &acc,
 }
 
 // First layer, from the frame itself.  A workgroup forms a 32 x 4 tile of
-// output pixels: it converts the 65 x 9 input pixels that the tile's taps
-// reach (RGB and residual as BF16, channels last, 16 bytes per pixel) into
-// LDS, writes those the tile owns to x_in (the backward pass reads them), and
+// output pixels: it converts the 65 x 9 input pixels that the tile's taps reach
+// (RGB and residual as BF16, channels last, 16 bytes per pixel) into LDS,
+// writes those the tile owns to x_in (the backward pass reads them), and
 // multiplies straight from LDS, one tap of one pixel per 16-byte read; waves 2
-// x 2, each 32 channels x 64 pixels with its weights in registers.  The
-// output tile goes through LDS so that whole 128-byte pixels are stored.  HBM
-// bound: 150 MB at 1920 x 1080 (frame, residual, x_in and the output), 37 us
-// (47 us with 64-bit addresses and a border test per load).  As two launches, a conversion and an implicit GEMM that read x_in back 2.25
-// times, it took 17 + 37 us; with the output stored from the accumulators (32
-// bytes of a pixel at a time) 57 us.
+// x 2, each 32 channels x 64 pixels with its weights in registers.  The output
+// tile goes through LDS so that whole 128-byte pixels are stored.  HBM bound:
+// 150 MB at 1920 x 1080 (frame, residual, x_in and the output), 37 us (47 us
+// with 64-bit addresses and a border test per load).  As two launches, a
+// conversion and an implicit GEMM that read x_in back 2.25 times, it took 17 +
+// 37 us; with the output stored from the accumulators (32 bytes of a pixel at a
+// time) 57 us.
 constexpr int C0_TW = 32, C0_TH = 4, C0_PW = 2 * C0_TW + 1, C0_PH = 2 * C0_TH + 1;
 constexpr int C0_N = C0_PW * C0_PH, C0_PER = (C0_N + 255) / 256;
 __global__ void __launch_bounds__(256)
@@ -149,7 +150,8 @@ k_conv_first(ConvArgs a, const float *__restrict__ frame, const float *__restric
   float f[C0_PER][3], q[C0_PER][3];
   size_t at[C0_PER];
   int own[C0_PER];
-  const __amdgpu_buffer_rsrc_t fb = buffer_of(frame, 12 * HW), qb = buffer_of(prev, prev ? 12 * HW : 0);
+  const __amdgpu_buffer_rsrc_t fb = buffer_of(frame, 12 * HW);
+  const __amdgpu_buffer_rsrc_t qb = buffer_of(prev, prev ? 12 * HW : 0);
   const int plane = (int)(4 * HW);
 #pragma unroll
   for (int j = 0; j < C0_PER; ++j) {
@@ -267,7 +269,8 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(ConvArgs a, int tiles_x, in
   uint4 av[18];
 #pragma unroll
   for (int k = 0; k < 18; ++k)
-    av[k] = *reinterpret_cast<const uint4 *>(a.w + (size_t)(m0 + 16 * w + r) * d.Kf + 32 * k + 8 * kg);
+    av[k] = *reinterpret_cast<const uint4 *>(a.w + (size_t)(m0 + 16 * w + r) * d.Kf + 32 * k +
+                                             8 * kg);
   const long long P = (long long)d.Hout * d.Wout;
   for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
     __syncthreads();
@@ -478,8 +481,9 @@ __global__ void __launch_bounds__(256) k_conv_bwd_data_head(ConvArgs a, int tile
   __syncthreads();
   if (!in) return;
   const uint4 o = *reinterpret_cast<const uint4 *>(out + (tid >> 3) * LP + 8 * c);
-  *reinterpret_cast<uint4 *>(a.dz_prev + at) = make_uint4(relu_mask(o.x, mask.x), relu_mask(o.y, mask.y),
-                                                          relu_mask(o.z, mask.z), relu_mask(o.w, mask.w));
+  *reinterpret_cast<uint4 *>(a.dz_prev + at) =
+      make_uint4(relu_mask(o.x, mask.x), relu_mask(o.y, mask.y), relu_mask(o.z, mask.z),
+                 relu_mask(o.w, mask.w));
 }
 
 // ----------------------------------------------------------- grad weight --
@@ -573,14 +577,16 @@ __device__ __forceinline__ void gw_layer(const GwLayer &L, int work, uint8_t *ld
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int e = tid + 512 * j, p = e >> 2;
-    fx[j] = e < NX ? (uint32_t)(p / PW * L.Win + p % PW) * 128u + 64u * half + 16u * (e & 3) : OUTSIDE;
+    fx[j] = e < NX ? (uint32_t)(p / PW * L.Win + p % PW) * 128u + 64u * half + 16u * (e & 3)
+                   : OUTSIDE;
   }
   const int zy = tid >> 6, zx = (tid >> 3) & 7;
   const uint32_t fz = m0 + 8 * (tid & 7) < L.CoutS
                           ? (uint32_t)((zy * L.Wout + zx) * L.CoutS + m0 + 8 * (tid & 7)) * 2u
                           : OUTSIDE;
   auto load = [&](Stage &v, int t) {
-    const int oy0 = t / L.tiles_x * 8, ox0 = t % L.tiles_x * 8, iy0 = oy0 * S - 1, ix0 = ox0 * S - 1;
+    const int oy0 = t / L.tiles_x * 8, ox0 = t % L.tiles_x * 8;
+    const int iy0 = oy0 * S - 1, ix0 = ox0 * S - 1;
     const int xbase = (iy0 * L.Win + ix0) * 128, zbase = (oy0 * L.Wout + ox0) * L.CoutS * 2;
     if (iy0 >= 0 && ix0 >= 0 && iy0 + PW <= L.Hin && ix0 + PW <= L.Win) {  // also within dZ
 #pragma unroll
@@ -677,9 +683,10 @@ __device__ __forceinline__ void gw_layer(const GwLayer &L, int work, uint8_t *ld
 
 // Layers 1 .. 4 in one launch of at most 256 workgroups, one per compute unit,
 // of equally many tiles each: a layer alone leaves most units idle (the fourth
-// has 135 tiles at 1920 x 1080), and fewer splits mean fewer partials (18 MB).  The grid is ordered so that the two channel
-// halves of a range of tiles run at the same time on one XCD (workgroup b is on
-// XCD b % 8) and share dZ and the 128-byte pixels in its L2.
+// has 135 tiles at 1920 x 1080), and fewer splits mean fewer partials (18 MB).
+// The grid is ordered so that the two channel halves of a range of tiles run at
+// the same time on one XCD (workgroup b is on XCD b % 8) and share dZ and the
+// 128-byte pixels in its L2.
 __global__ void __launch_bounds__(512, 2) k_conv_bwd_weight(GwArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[GW_LDS + GW_ZERO];
   const int per_xcd = (int)(gridDim.x >> 3);

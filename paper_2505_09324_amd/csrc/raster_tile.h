@@ -198,12 +198,13 @@ __device__ inline void stage_chunk(Smem<C> &S, const uint32_t *__restrict__ keys
     if constexpr (EXACT) {
       const float sq = __builtin_amdgcn_sqrtf(qmax), ia = __builtin_amdgcn_rcpf(a);
       // the centre and the last pixel column, from the tile's first
-      const float left = g0.x - ((float)(tx * TILE) + 0.5f), xl = xlast - ((float)(tx * TILE) + 0.5f);
+      const float first = (float)(tx * TILE) + 0.5f, left = g0.x - first, xl = xlast - first;
       for (int by = by0; by <= by1; ++by) {
         const float Y0 = (float)(ty * TILE + by * C::SBH) + 0.5f;
         const float Y1 = fminf(Y0 + (float)(C::SBH - 1), ylast);
         float u0, u1;
-        if (Y0 > Y1 || !ellipse_in_strip(l2s, r3s, Y0 - g0.y, Y1 - g0.y, qmax, sq, &u0, &u1)) continue;
+        if (Y0 > Y1 || !ellipse_in_strip(l2s, r3s, Y0 - g0.y, Y1 - g0.y, qmax, sq, &u0, &u1))
+          continue;
         // columns from the first whose last pixel is not left of the cut, to
         // the last whose first is not right of it; the box's after a NaN
         const bool cut = u0 <= u1;
@@ -304,6 +305,13 @@ __device__ inline void pixel_of_thread(int tx, int ty, int *px, int *py0, int pa
   *py0 = ty * TILE + (w / C::SBX) * C::SBH + (lane >> 3) * PPL;
 }
 
+// q' of a pixel.  The same expression, rounding for rounding, wherever a pair is
+// evaluated: the cutoff must hold for the same pixels in every pass and route.
+template <int PPL>
+__device__ __forceinline__ float pair_q(float u1, float u1s, float u2) {
+  return PPL == 1 ? __builtin_fmaf(u1, u1, u2 * u2) : __builtin_fmaf(u2, u2, u1s);
+}
+
 // Forward accumulation over entries [beg, end) of this wavefront's list of a
 // staged, compacted chunk.  With KEEP_HITS (the whole list: beg = 0) the
 // wavefront's list is compacted in place to the Gaussians that have at least
@@ -324,7 +332,7 @@ __device__ inline int fwd_chunk(Smem<C> &S, int beg, int end, float pxc, float p
     float u2 = base * B.x;  // the next pixel row adds 1/l3 (staged units)
 #pragma unroll
     for (int r = 0; r < PPL; ++r, u2 += B.x) {
-      const float q = u1s + u2 * u2;
+      const float q = pair_q<PPL>(u1, u1s, u2);
       const float e = __builtin_amdgcn_exp2f(-q);
       const bool in_cut = q <= CUTOFF_QS;
       const float wgt = in_cut ? e : 0.f;
@@ -367,7 +375,8 @@ __device__ inline void exchange_sums(float *xch, float (&acc)[PPL][3]) {
 // with the colour B.yzw, and its share `wgt` added to the sums c.  s_nop: a
 // register that a DPP operand reads must be two states old.
 template <int N>
-__device__ __forceinline__ float row_pixel(const float (&g)[3], const float4 &B, float wgt, float *c) {
+__device__ __forceinline__ float row_pixel(const float (&g)[3], const float4 &B, float wgt,
+                                           float *c) {
   float d;
   asm("s_nop 1\n"
       "v_mul_f32_dpp %0, %4, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
@@ -389,13 +398,14 @@ struct BatchSums {
 };
 template <int PPL, bool CHECK_HITS, int N>
 __device__ __forceinline__ void batch_pixels(BatchSums &T, float &t0, float &t2, const float4 &B,
-                                             float u1s, float base, const float (&g)[PPL][3]) {
+                                             float cut, float u1, float u1s, float base,
+                                             const float (&g)[PPL][3]) {
   float u2 = base * B.x;  // the next pixel row adds 1/l3
 #pragma unroll
   for (int r = 0; r < PPL; ++r, u2 += B.x) {
-    const float q = u1s + u2 * u2;
+    const float q = pair_q<PPL>(u1, u1s, u2);
     const float e = __builtin_amdgcn_exp2f(-q);
-    const bool in_cut = q <= CUTOFF_QS;
+    const bool in_cut = q <= cut;
     const float wgt = in_cut ? e : 0.f;
     if (CHECK_HITS) T.any |= in_cut;
     const float sn = row_pixel<N>(g[r], B, wgt, T.v + 5) * wgt;
@@ -406,20 +416,21 @@ __device__ __forceinline__ void batch_pixels(BatchSums &T, float &t0, float &t2,
   }
 }
 template <int PPL, bool CHECK_HITS, int COL>
-__device__ __forceinline__ void batch_column(BatchSums &T, const float4 &A, const float4 &B, bool live,
-                                             float x0, const float (&yb)[2], const float (&g)[PPL][3]) {
+__device__ __forceinline__ void batch_column(BatchSums &T, const float4 &A, const float4 &B,
+                                             float cut, float x0, const float (&yb)[2],
+                                             const float (&g)[PPL][3]) {
   const float u1 = ((x0 + (float)COL) - A.x) * A.z;
-  const float u1s = live ? u1 * u1 : INFINITY;
+  const float u1s = u1 * u1;
   float t0 = 0.f, t2 = 0.f;
-  batch_pixels<PPL, CHECK_HITS, COL>(T, t0, t2, B, u1s, yb[0] - A.w * u1, g);
-  batch_pixels<PPL, CHECK_HITS, COL + 8>(T, t0, t2, B, u1s, yb[1] - A.w * u1, g);
+  batch_pixels<PPL, CHECK_HITS, COL>(T, t0, t2, B, cut, u1, u1s, yb[0] - A.w * u1, g);
+  batch_pixels<PPL, CHECK_HITS, COL + 8>(T, t0, t2, B, cut, u1, u1s, yb[1] - A.w * u1, g);
   t2 *= B.x;
   const float s1 = u1 * t0 - A.w * t2;
   T.v[0] += s1;
   T.v[1] += t2;
   T.v[2] += s1 * u1;
   T.v[3] += t2 * u1;
-  if constexpr (COL < 7) batch_column<PPL, CHECK_HITS, COL + 1>(T, A, B, live, x0, yb, g);
+  if constexpr (COL < 7) batch_column<PPL, CHECK_HITS, COL + 1>(T, A, B, cut, x0, yb, g);
 }
 
 // Backward of up to 16 Gaussians at once, entries [k0, min(k0 + 16, end)): lane
@@ -444,7 +455,7 @@ __device__ __forceinline__ void bwd_batch(const Smem<C> &S, float *acc, int k0, 
   const float y0 = pyc0 - (float)(((lane >> 3) & 1) * PPL);  // the row's first pixel row
   const float yb[2] = {y0 - A.y, (y0 + (float)PPL) - A.y};
   BatchSums T = {};
-  batch_column<PPL, CHECK_HITS, 0>(T, A, B, live, x0, yb, g);
+  batch_column<PPL, CHECK_HITS, 0>(T, A, B, live ? CUTOFF_QS : -1.f, x0, yb, g);
   T.v[0] *= A.z;
   T.v[2] *= A.z;
   T.v[4] *= B.x;
@@ -505,7 +516,7 @@ __device__ inline void bwd_chunk(const Smem<C> &S, float *acc, int beg, int end,
 #pragma unroll
     for (int r = 0; r < PPL; ++r) {
       u2[r] = r == 0 ? base * B.x : u2[r - 1] + B.x;  // the next pixel row adds 1/l3
-      q[r] = u1s + u2[r] * u2[r];
+      q[r] = pair_q<PPL>(u1, u1s, u2[r]);
       any |= q[r] <= CUTOFF_QS;
     }
     if (CHECK_HITS && !__ballot(any)) continue;  // wavefront-uniform skip
@@ -671,7 +682,8 @@ __device__ inline void fused_tile(Smem<C> &S, float *acc, float *xch, const Fram
   for (int c = beg; c < end; c += C::CH) {
     const int cnt = min(C::CH, end - c);
     if (!ONE || c != beg) __syncthreads();  // LDS of a previous tile or chunk is free
-    stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active, part);
+    stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active,
+                                part);
     if (once)
       for (int i = threadIdx.x; i < cnt * 8; i += C::NT) acc[i] = 0.f;
     __syncthreads();
@@ -687,7 +699,8 @@ __device__ inline void fused_tile(Smem<C> &S, float *acc, float *xch, const Fram
     const int cnt = min(C::CH, end - c);
     if (!once) {
       __syncthreads();
-      stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active, part);
+      stage_chunk<C, TILE, EXACT>(S, f.keys, c, cnt, tx, ty, f.W, f.H, f.geom, f.rgb, f.active,
+                                  part);
       for (int i = threadIdx.x; i < cnt * 8; i += C::NT) acc[i] = 0.f;
       __syncthreads();
       len = compact_chunk<C>(S, cnt);

@@ -54,20 +54,21 @@ struct Cfg {
 // slowest wavefront is done, so smaller ones leave a shorter tail at the end
 // of a launch and fewer idle wavefronts before each barrier, at the price of
 // staging the tile's list once per part.  Fits of 20 iterations at 1920x1080 /
-// 30,000, us: 32/2 (8 sub-blocks) whole 1345, halves 1300, quarters 1431;
-// 32/1 (16) whole 1645, halves 1453, quarters 1364; 32/4 and the 16-pixel
-// tiles (4 and 2) do not gain.
+// 30,000, us: 32/2 (8 sub-blocks) whole 1202, halves 1126, quarters 1208; 32/1
+// (16) whole 1284, halves 1300, quarters 1200; halves of 16/1 2301 against 1971,
+// of 16/2 2136 against 1854, of 32/4 no gain.
 #define GS2D_VARIANTS(X) \
   X(8, 1, 1, 1) X(16, 1, 1, 1) X(16, 2, 1, 1) X(32, 1, 4, 4) X(32, 2, 2, 4) X(32, 4, 1, 2)
 
 // LS: the device holds 8192 wavefronts.  A frame with at most a quarter as
 // many sub-blocks is bound by the serial pass over each one's list, so four
-// wavefronts share it; up to a half, two.  us per iteration at 480x270 / 1200
-// (32/2: 1080 sub-blocks) 27.5 -> 20.8, 640x360 / 1000 (1920) 24.6 -> 20.5 and
-// at 960x540 / 7000 (4080) 34.6 -> 31.7; at 1280x720 (7360) two are no faster,
-// and at 16/1 four at 3680 sub-blocks are slower than one (24.5 against 23.7).
+// wavefronts share it; somewhat below a half, two.  us per iteration at
+// 480x270 / 1200 (32/2: 1080 sub-blocks) alone 22.4, four 19.2; 640x360 / 1000
+// (1920) 20.5, 19.1; 800x450 / 4500 (3000) alone 27.4, two 25.6, four 28.5;
+// 640x360 with 16/1 (3680) 21.9, 20.9, 24.6; 960x540 / 7000 (4080) 28.4, 30.0,
+// 32.0; at 1280x720 (7360) two take 38.5 against 34.3.
 inline int raster_share(long long sub_blocks) {
-  return sub_blocks <= 2048 ? 4 : sub_blocks <= 4096 ? 2 : 1;
+  return sub_blocks <= 2048 ? 4 : sub_blocks <= 3840 ? 2 : 1;
 }
 
 // The workgroup's tile (or work item) and its part of it: the parts run on one
@@ -490,7 +491,7 @@ __device__ __forceinline__ void bwd_batch(const Smem<C> &S, float *acc, int k0, 
 // iterations at 1920x1080 / 30,000, from 8: 1146, from 10: 1151, full batches
 // only: 1200, never: 1296).  Where four wavefronts share a list they split it
 // finer than that (640x360 / 1000, 50 iterations: 962 without, 989 with); two
-// gain (960x540 / 7000: 645 without, 607 with).
+// gain.
 constexpr int BATCH_MIN = 8;
 
 // Backward over entries [beg, end) of this wavefront's list of a staged,

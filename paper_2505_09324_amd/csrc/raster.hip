@@ -1,14 +1,14 @@
 // Tile rasteriser for Eq. 2 (accumulated summation, Sec. 3.1) and its
 // backward pass.
 //
-// One workgroup per TILE x TILE screen tile.  Each wavefront owns a sub-block
+// SPLIT workgroups per TILE x TILE screen tile.  Each wavefront owns a sub-block
 // 8 pixels wide and 8*PPL pixels tall: lane (lx, ly) = (lane & 7, lane >> 3)
 // handles the PPL vertically adjacent pixels (x0 + lx, y0 + ly*PPL + k),
 // which share d_x, u1 = d_x / l1 and u1^2.  The tile's Gaussian list is
 // staged through LDS in chunks; while staging, each Gaussian's 3-sigma box
-// and then its cutoff ellipse are tested against every sub-block, and each
-// wavefront compacts the chunk into its own list of the Gaussians that can
-// reach its sub-block's pixels.
+// and its cutoff ellipse's cut with each row of sub-blocks select the
+// sub-blocks it can reach, and each wavefront compacts the chunk into its own
+// list.
 //
 // Per (pixel, Gaussian), with d = (x+1/2, y+1/2) - mu and u = L^-1 d:
 //   u1 = d1 / l1;  u2 = (d2 - l2 u1) / l3;  q = u1^2 + u2^2
@@ -16,10 +16,12 @@
 // Backward, with g = dL/dC at the pixel, s = (g . c') w, v = L^-T u:
 //   dL/dmu += s v;  dL/dl1 += s v1 u1;  dL/dl2 += s v2 u1;  dL/dl3 += s v2 u2;
 //   dL/dc' += g w.
-// The eight per-lane sums of one Gaussian are reduced across the wavefront
-// by a transposing butterfly (each exchange halves the values a lane
-// carries), added into an LDS accumulator shared by the tile's wavefronts,
-// and flushed with one global atomic per (tile, Gaussian, parameter).
+// The backward takes 16 Gaussians of a list at a time, each lane summing one
+// over its row's pixels; those left over go one by one, their eight per-lane
+// sums reduced across the wavefront by a transposing butterfly (each exchange
+// halves the values a lane carries).  The sums are added into an LDS accumulator
+// shared by the workgroup's wavefronts and flushed with one global atomic per
+// (workgroup, Gaussian, parameter).
 #include "raster_tile.h"
 
 namespace gs2d {

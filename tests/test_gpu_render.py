@@ -323,7 +323,7 @@ def test_fused_long_lists_every_variant():
         assert_grads_close({"xy": host(g[0]), "chol": host(g[1]), "rgb": host(g[2])}, want)
 
 
-@pytest.mark.parametrize("W,H", [(400, 300), (640, 400), (1100, 1000)])
+@pytest.mark.parametrize("W,H", [(400, 300), (600, 400), (640, 400), (1100, 1000)])
 def test_every_route_at_frame_sizes(W, H):
     """Frames whose number of sub-blocks makes four, two or one wavefront
     share a sub-block (every variant meets all three over the sizes), with

@@ -815,11 +815,81 @@ __global__ void __launch_bounds__(256) k_gw_reduce(GwArgs a) {
 
 __device__ inline float sigm(float z) { return 1.f / (1.f + __expf(-z)); }
 
+// x of lane N of this lane's row of 16; sum and largest over the row.
+template <int CTRL>
+__device__ __forceinline__ float row_dpp(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+template <int N>
+__device__ __forceinline__ float row_lane(float x) {
+  return row_dpp<0x150 + N>(x);
+}
+// quad_perm [1,0,3,2] and [2,3,0,1], row_half_mirror, row_ror:8
+__device__ __forceinline__ float row_sum(float x) {
+  x += row_dpp<0xB1>(x);
+  x += row_dpp<0x4E>(x);
+  x += row_dpp<0x141>(x);
+  return x + row_dpp<0x128>(x);
+}
+__device__ __forceinline__ float row_max(float x) {
+  x = fmaxf(x, row_dpp<0xB1>(x));
+  x = fmaxf(x, row_dpp<0x4E>(x));
+  x = fmaxf(x, row_dpp<0x141>(x));
+  return fmaxf(x, row_dpp<0x128>(x));
+}
+
+// Prediction s -> nearest target (first minimum), targets N and on.
+template <int N>
+__device__ __forceinline__ void nearest_target(const float (&Pv)[NPAR], const float (&Qv)[NPAR],
+                                               int k, float &bd, float (&Qb)[NPAR]) {
+  float Qq[NPAR], dd = 0.f;
+#pragma unroll
+  for (int j = 0; j < NPAR; ++j) {
+    Qq[j] = row_lane<N>(Qv[j]);
+    dd += (Pv[j] - Qq[j]) * (Pv[j] - Qq[j]);
+  }
+  if (N < k && dd < bd) {
+    bd = dd;
+#pragma unroll
+    for (int j = 0; j < NPAR; ++j) Qb[j] = Qq[j];
+  }
+  if constexpr (N + 1 < NSLOT) nearest_target<N + 1>(Pv, Qv, k, bd, Qb);
+}
+// Target s -> nearest prediction (first minimum).
+template <int N>
+__device__ __forceinline__ void nearest_prediction(const float (&Pv)[NPAR],
+                                                   const float (&Qv)[NPAR], int k, float &bd,
+                                                   int &best) {
+  float dd = 0.f;
+#pragma unroll
+  for (int j = 0; j < NPAR; ++j) {
+    const float Ps = row_lane<N>(Pv[j]);
+    dd += (Ps - Qv[j]) * (Ps - Qv[j]);
+  }
+  if (N < k && dd < bd) bd = dd, best = N;
+  if constexpr (N + 1 < NSLOT) nearest_prediction<N + 1>(Pv, Qv, k, bd, best);
+}
+// Adds the targets whose nearest prediction is s to its gradient.
+template <int N>
+__device__ __forceinline__ void pull_targets(const float (&Pv)[NPAR], const float (&Qv)[NPAR],
+                                             int k, int s, int best, float inv_k,
+                                             float (&gp)[NPAR]) {
+  const int b = __float_as_int(row_lane<N>(__int_as_float(best)));
+#pragma unroll
+  for (int j = 0; j < NPAR; ++j) {
+    const float Qq = row_lane<N>(Qv[j]);
+    if (N < k && b == s) gp[j] += 2.f * (Pv[j] - Qq) * inv_k;
+  }
+  if constexpr (N + 1 < NSLOT) pull_targets<N + 1>(Pv, Qv, k, s, best, inv_k, gp);
+}
+
 // Per-tile loss: CE over the 9 count logits + Chamfer between the first k
 // slots and the k targets (8-vectors).  16 lanes per tile: lane c < 9 holds
 // count logit c, lane s < 8 holds prediction slot s and target s.  The head
 // gradient goes out as dZ of the head (BF16 [n_tiles][CoutS]); per-tile loss
-// sums to tile_loss (CE, CD).
+// sums to tile_loss (CE, CD).  The 16 lanes are a DPP row, so a value of lane n
+// reaches the others as a register move (as LDS permutes, 200 of them per tile,
+// the launch took 7.7 us at 1920 x 1080; 5.4 with moves).
 __global__ void __launch_bounds__(256)
 k_head_loss(int n_tiles, int CoutS, const float *__restrict__ head, const int *__restrict__ tcount,
             const float *__restrict__ tvec, const int *__restrict__ n_cd_dev,
@@ -833,10 +903,8 @@ k_head_loss(int n_tiles, int CoutS, const float *__restrict__ head, const int *_
   const int k = min(max(tcount[tt], 0), NSLOT);
   // cross entropy of the count logits
   const float z = (l < 9) ? head[(size_t)l * n_tiles + tt] : -INFINITY;
-  float mx = z;
-  for (int o = 1; o < 16; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  float se = (l < 9) ? __expf(z - mx) : 0.f;
-  for (int o = 1; o < 16; o <<= 1) se += __shfl_xor(se, o, 64);
+  const float mx = row_max(z);
+  const float se = row_sum((l < 9) ? __expf(z - mx) : 0.f);
   const float lse = mx + __logf(se);
   const float zk = __shfl(z, base + k, 64);
   const float ce = lse - zk;
@@ -856,45 +924,17 @@ k_head_loss(int n_tiles, int CoutS, const float *__restrict__ head, const int *_
   float bd = INFINITY, Qb[NPAR];
 #pragma unroll
   for (int j = 0; j < NPAR; ++j) Qb[j] = 0.f;
-  for (int qq = 0; qq < NSLOT; ++qq) {
-    float Qq[NPAR], dd = 0.f;
-#pragma unroll
-    for (int j = 0; j < NPAR; ++j) {
-      Qq[j] = __shfl(Qv[j], base + qq, 64);
-      dd += (Pv[j] - Qq[j]) * (Pv[j] - Qq[j]);
-    }
-    if (qq < k && dd < bd) {
-      bd = dd;
-#pragma unroll
-      for (int j = 0; j < NPAR; ++j) Qb[j] = Qq[j];
-    }
-  }
+  nearest_target<0>(Pv, Qv, k, bd, Qb);
   // target s -> nearest prediction (first minimum)
   float bd2 = INFINITY;
   int best2 = 0;
-  for (int ss = 0; ss < NSLOT; ++ss) {
-    float dd = 0.f;
-#pragma unroll
-    for (int j = 0; j < NPAR; ++j) {
-      const float Ps = __shfl(Pv[j], base + ss, 64);
-      dd += (Ps - Qv[j]) * (Ps - Qv[j]);
-    }
-    if (ss < k && dd < bd2) bd2 = dd, best2 = ss;
-  }
+  nearest_prediction<0>(Pv, Qv, k, bd2, best2);
   const bool own = l < 8 && s < k;
-  float cd = own ? (bd + bd2) * inv_k : 0.f;
-  for (int o = 1; o < 16; o <<= 1) cd += __shfl_xor(cd, o, 64);
+  const float cd = row_sum(own ? (bd + bd2) * inv_k : 0.f);
   float gp[NPAR];
 #pragma unroll
   for (int j = 0; j < NPAR; ++j) gp[j] = 2.f * (Pv[j] - Qb[j]) * inv_k;
-  for (int qq = 0; qq < NSLOT; ++qq) {  // targets whose nearest prediction is s
-    const int b = __shfl(best2, base + qq, 64);
-#pragma unroll
-    for (int j = 0; j < NPAR; ++j) {
-      const float Qq = __shfl(Qv[j], base + qq, 64);
-      if (qq < k && b == s) gp[j] += 2.f * (Pv[j] - Qq) * inv_k;
-    }
-  }
+  pull_targets<0>(Pv, Qv, k, s, best2, inv_k, gp);
   if (!live) return;
   uint16_t *out = dz + (size_t)t * CoutS;
   if (l < 9) out[l] = f2bf(gce);

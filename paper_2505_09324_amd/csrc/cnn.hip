@@ -792,11 +792,60 @@ __global__ void __launch_bounds__(256, 2) k_conv_bwd_weight_first(GwLayer L) {
   }
 }
 
+// The losses from the tiles': out = total, cross entropy, Chamfer.
+struct LossSum {
+  int n_tiles;
+  const float *tile_loss;
+  const int *n_cd;
+  float *out;
+};
+__device__ __forceinline__ void sum_losses(const LossSum &L) {
+  __shared__ double red[2][4];
+  double ce = 0.0, cd = 0.0;
+  // 16 loads in flight: the launch waits for this one workgroup
+  for (int t0 = threadIdx.x; t0 < L.n_tiles; t0 += 16 * 256) {
+    float2 v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      v[j] = *reinterpret_cast<const float2 *>(L.tile_loss +
+                                               2 * min(t0 + 256 * j, L.n_tiles - 1));
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const bool in = t0 + 256 * j < L.n_tiles;
+      ce += in ? v[j].x : 0.f;
+      cd += in ? v[j].y : 0.f;
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    ce += __shfl_xor(ce, o, 64);
+    cd += __shfl_xor(cd, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = ce;
+    red[1][threadIdx.x >> 6] = cd;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double c1 = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+    const double c2 = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+    const int n_cd = *L.n_cd;
+    L.out[0] = (float)(c1 / L.n_tiles + (n_cd > 0 ? c2 / n_cd : 0.0));
+    L.out[1] = (float)(c1 / L.n_tiles);
+    L.out[2] = (float)(n_cd > 0 ? c2 / n_cd : 0.0);
+  }
+}
+
 // Sum of the partials over the splits, added into dW and dbias: one workgroup
-// per column (64 rows) of every layer, four lanes' worth of splits each.
-__global__ void __launch_bounds__(256) k_gw_reduce(GwArgs a) {
+// per column (64 rows) of every layer, four lanes' worth of splits each.  The
+// first workgroup sums the losses: as a launch of its own that took 4 us of a
+// 247 us training step at 1920 x 1080 and 11 of 753 at 3840 x 2160.
+__global__ void __launch_bounds__(256) k_gw_reduce(GwArgs a, LossSum loss) {
   __shared__ float red[256];
-  int b = blockIdx.x, l = 0;
+  if (blockIdx.x == 0) {
+    if (loss.out) sum_losses(loss);
+    return;
+  }
+  int b = blockIdx.x - 1, l = 0;
   while (b >= a.L[l].mt * (a.L[l].cols + 1)) b -= a.L[l].mt * (a.L[l].cols + 1), ++l;
   const GwLayer &L = a.L[l];
   const int tid = threadIdx.x, mt = b / (L.cols + 1), c = b - mt * (L.cols + 1);
@@ -955,38 +1004,6 @@ k_head_loss(int n_tiles, int CoutS, const float *__restrict__ head, const int *_
   if (l == 0) {
     tile_loss[2 * t] = ce;
     tile_loss[2 * t + 1] = cd;
-  }
-}
-
-__global__ void __launch_bounds__(1024)
-k_loss_sum(int n_tiles, const float *__restrict__ tile_loss, const int *__restrict__ n_cd_dev,
-           float *__restrict__ out) {
-  __shared__ double red[2][16];
-  double ce = 0.0, cd = 0.0;
-  for (int t = threadIdx.x; t < n_tiles; t += 1024) {
-    const float2 v = *reinterpret_cast<const float2 *>(tile_loss + 2 * t);
-    ce += v.x;
-    cd += v.y;
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    ce += __shfl_xor(ce, o, 64);
-    cd += __shfl_xor(cd, o, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = ce;
-    red[1][threadIdx.x >> 6] = cd;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double c1 = 0.0, c2 = 0.0;
-    for (int w = 0; w < 16; ++w) {
-      c1 += red[0][w];
-      c2 += red[1][w];
-    }
-    const int n_cd = *n_cd_dev;
-    out[0] = (float)(c1 / n_tiles + (n_cd > 0 ? c2 / n_cd : 0.0));
-    out[1] = (float)(c1 / n_tiles);
-    out[2] = (float)(n_cd > 0 ? c2 / n_cd : 0.0);
   }
 }
 
@@ -1864,9 +1881,6 @@ int gs2d_cnn_backward(int32_t H, int32_t W, const float *master, const uint16_t 
                      at<const int>(ws, C.tcount), at<const float>(ws, C.tvec),
                      at<const int>(ws, C.ncd), at<uint16_t>(ws, C.dz[NLAYER - 1]),
                      at<float>(ws, C.tile_loss));
-  if (loss3)
-    hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(1024), 0, st, C.n_tiles,
-                       at<const float>(ws, C.tile_loss), at<const int>(ws, C.ncd), loss3);
   const uint16_t *wt = wbf16 + C.n_wb;
   GwArgs gw = C.gw;
   int cols = 0;
@@ -1892,7 +1906,9 @@ int gs2d_cnn_backward(int32_t H, int32_t W, const float *master, const uint16_t 
                      gw);
   hipLaunchKernelGGL(k_conv_bwd_weight_first, dim3((unsigned)gw.L[0].splits), dim3(256), 0, st,
                      gw.L[0]);
-  hipLaunchKernelGGL(k_gw_reduce, dim3((unsigned)cols), dim3(256), 0, st, gw);
+  hipLaunchKernelGGL(k_gw_reduce, dim3((unsigned)cols + 1), dim3(256), 0, st, gw,
+                     LossSum{C.n_tiles, at<const float>(ws, C.tile_loss), at<const int>(ws, C.ncd),
+                             loss3});
   return hipGetLastError() == hipSuccess ? GS2D_OK : GS2D_EHIP;
 }
 

@@ -438,3 +438,31 @@ def test_cnn_adam_matches_oracle_decoupled_decay():
 @pytest.mark.parametrize("hw", [(64, 64), (66, 130), (60, 124), (520, 600)])
 def test_layers_at_tile_edges(hw):
     test_layers_elementwise_against_oracle(hw)
+
+
+# the losses are summed by one workgroup, 4096 tiles a pass: one tile, a lane
+# more than the workgroup has, one full pass, a second one of 64 tiles
+@pytest.mark.parametrize("hw", [(16, 16), (16, 4112), (1024, 1024), (1024, 1040)])
+def test_loss_sum_over_tiles(hw):
+    """All three losses against FP64 sums over the tiles.  A tile's terms are
+    a few FP32 operations (1e-6 relative), and a Chamfer term loses at most
+    another digit where prediction and target are close; one tile lost of
+    4160 would be 2.4e-4."""
+    H, W = hw
+    print("cnn loss sum", hw, flush=True)
+    f0, f1 = _frames(61, hw)
+    n = max(4, 3 * H * W // 256)
+    xy, chol, rgb = synth.random_gaussians(n, W, H, seed=62, scale_lo=0.6, scale_hi=3.0)
+    net = _lib.CNNInit(H, W, seed=63)
+    net.set_targets(dev(xy), dev(chol), dev(rgb))
+    head = torch.empty(73, net.TY, net.TX, device=DEV)
+    net.forward(dev(f1), dev(f0), head_out=head)
+    loss = host(net.backward())
+    counts, vec = (host(v) for v in net.read_targets())
+    vec = vec.reshape(counts.size, 8, 8).astype(np.float64)
+    targets = {t: vec[t, :counts.ravel()[t]] for t in range(counts.size)}
+    hd = host(head).astype(np.float64)
+    total, _ = ocnn.head_loss(hd, targets)
+    ce = np.mean([ocnn.cross_entropy(ocnn.slot_vectors(hd[:, t // net.TX, t % net.TX])[0],
+                                     len(targets[t]))[0] for t in range(counts.size)])
+    np.testing.assert_allclose(loss, [total, ce, total - ce], rtol=2e-5)

@@ -938,7 +938,7 @@ __device__ __forceinline__ void pull_targets(const float (&Pv)[NPAR], const floa
 // gradient goes out as dZ of the head (BF16 [n_tiles][CoutS]); per-tile loss
 // sums to tile_loss (CE, CD).  The 16 lanes are a DPP row, so a value of lane n
 // reaches the others as a register move (as LDS permutes, 200 of them per tile,
-// the launch took 7.7 us at 1920 x 1080; 5.4 with moves).
+// the launch took 7.7 us at 1920 x 1080; 5.4 to 6.1 with moves).
 __global__ void __launch_bounds__(256)
 k_head_loss(int n_tiles, int CoutS, const float *__restrict__ head, const int *__restrict__ tcount,
             const float *__restrict__ tvec, const int *__restrict__ n_cd_dev,

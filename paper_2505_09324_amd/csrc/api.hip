@@ -292,7 +292,7 @@ hipError_t enqueue_iterations(const Layout &L, void *ws, const float *target, fl
       }
       if (e == hipSuccess)
         e = launch_render_fused(L, ws, q_rgb, target, g_xy, g_chol, g_rgb, st, active, skin > 0.f,
-                                skin > 0.f ? step : nullptr);
+                                skin > 0.f ? step : nullptr, true);
       if (e == hipSuccess)
         e = L.wide ? launch_adam_extremes(pending, L.N, part, report, st)
                    : launch_adam(L.N, xy, chol, rgb, g_xy, g_chol, g_rgb, m, v, step, cfg, active,

@@ -209,10 +209,13 @@ hipError_t launch_render_bwd(const Layout &L, void *ws, const float *rgb, const 
 // lazy: the launch also clears misc[MISC_STALE] and, when it was set,
 // stamps the rebuilt lists (FrameArgs::lazy_misc).
 // tick (nullable): the launch also adds 1 to *tick (the step counter).
+// fixed_sums: one workgroup per tile, one wavefront per sub-block and one
+// Gaussian at a time in the backward, whatever the frame (quantisation-aware
+// fits).
 hipError_t launch_render_fused(const Layout &L, void *ws, const float *rgb, const float *target,
                                float *g_xy, float *g_chol, float *g_rgb, hipStream_t st,
                                const uint8_t *active = nullptr, bool lazy = false,
-                               int32_t *tick = nullptr);
+                               int32_t *tick = nullptr, bool fixed_sums = false);
 hipError_t launch_loss_reduce(const Layout &L, void *ws, float *loss, hipStream_t st);
 hipError_t launch_count_pairs(const Layout &L, void *ws, unsigned long long *out, hipStream_t st);
 

@@ -498,12 +498,13 @@ constexpr int BATCH_MIN = 8;
 // compacted chunk; adds into acc[CH][8] in LDS.
 // CHECK_HITS skips (uniformly per wavefront) Gaussians with no pixel inside
 // the cutoff, for lists that were not already reduced to such Gaussians.
-template <class C, int PPL, bool CHECK_HITS>
+// BATCH false: one Gaussian at a time whatever the list's length.
+template <class C, int PPL, bool CHECK_HITS, bool BATCH = true>
 __device__ inline void bwd_chunk(const Smem<C> &S, float *acc, int beg, int end, float pxc,
                                  float pyc0, const float (&g)[PPL][3]) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int k = beg;
-  if constexpr (C::NW <= 2 * C::NB)
+  if constexpr (BATCH && C::NW <= 2 * C::NB)
     for (; end - k >= BATCH_MIN; k += 16)
       bwd_batch<C, PPL, CHECK_HITS>(S, acc, k, end, pxc, pyc0, g);
   for (; k < end; ++k) {
@@ -650,7 +651,7 @@ __device__ inline void residuals(const float (&a)[PPL][3], const float (&tg)[PPL
 
 // ONE: the caller runs one tile per workgroup (no LDS of an earlier tile to
 // wait for before staging).  loss_slots: the tile's, one per sub-block.
-template <class C, int TILE, int PPL, bool EXACT = true, bool ONE = false>
+template <class C, int TILE, int PPL, bool EXACT = true, bool ONE = false, bool BATCH = true>
 __device__ inline void fused_tile(Smem<C> &S, float *acc, float *xch, const FrameArgs &f, int tile,
                                   const float *__restrict__ target,
                                   float *__restrict__ loss_slots, float grad_scale,
@@ -708,7 +709,7 @@ __device__ inline void fused_tile(Smem<C> &S, float *acc, float *xch, const Fram
     }
     if (f.active) len = keep_active<C>(S, len);
     list_run<C>(len, &kb, &ke);
-    bwd_chunk<C, PPL, !EXACT>(S, acc, kb, ke, pxc, pyc0, g);
+    bwd_chunk<C, PPL, !EXACT, BATCH>(S, acc, kb, ke, pxc, pyc0, g);
     __syncthreads();
     flush_grads<C, ONE>(S, acc, cnt, g_xy, g_chol, g_rgb);
   }

@@ -135,3 +135,81 @@ def test_quantisation_aware_routes_agree(N):
     for tr in out[1:]:
         assert abs(tr[0] - out[0][0]) <= 1e-6 * out[0][0]
         np.testing.assert_allclose(tr, out[0], rtol=1e-3)
+
+
+def _one_sub_block_each(W, H, ppl, seed):
+    """Gaussians that stay inside one 8 x 8 ppl block of pixels each, 13 or 5
+    to a block, on a frame of noise: a Gaussian's gradient is then the sum of
+    one wavefront, and no order of atomics enters it."""
+    rng = np.random.default_rng(seed)
+    nx = W // 8
+    xy = []
+    for i, c in enumerate(rng.permutation(nx * (H // (8 * ppl)))[:60]):
+        n = 5 if i % 3 == 0 else 13
+        xy.append(np.stack([c % nx * 8 + 4 + rng.uniform(-.2, .2, n),
+                            (c // nx + .5) * 8 * ppl + rng.uniform(-.2, .2, n)], 1))
+    xy = np.concatenate(xy).astype(np.float32)
+    N = len(xy)
+    chol = np.stack([rng.uniform(.5, .8, N), rng.uniform(-.2, .2, N), rng.uniform(.5, .8, N)], 1)
+    return (xy, chol.astype(np.float32), rng.normal(.2, .2, (N, 3)).astype(np.float32),
+            rng.uniform(0, 1, (3, H, W)).astype(np.float32))
+
+
+def _adam_start(params):
+    N = len(params[0])
+    return [dev(p) for p in params] + [torch.zeros(8 * N, device=DEV),
+                                       torch.zeros(8 * N, device=DEV),
+                                       torch.zeros(1, dtype=torch.int32, device=DEV)]
+
+
+@pytest.mark.parametrize("W,H,tile,ppl", [(640, 480, 8, 1), (1000, 700, 16, 1), (1280, 736, 16, 2),
+                                          (1280, 720, 32, 1), (1280, 720, 32, 2),
+                                          (1920, 1080, 32, 4)])
+def test_quantisation_aware_gradients_are_summed_one_gaussian_at_a_time(W, H, tile, ppl):
+    """Three steps, parameters and moments bit for bit those of the same
+    steps by single calls: quantise, bin, render, the gradients of at most
+    seven Gaussians per call (too few for the backward's batches), Adam."""
+    print(f"qat sums {W}x{H} {tile}/{ppl}", flush=True)
+    xy, chol, rgb, frame = _one_sub_block_each(W, H, ppl, 5)
+    N, target, cfg = len(xy), dev(frame), _lib.adam_cfg((2e-2, 5e-3, 5e-3))
+    fit, ref = _adam_start((xy, chol, rgb)), _adam_start((xy, chol, rgb))
+    f, r, trace = GpuFrame(W, H, N, tile, ppl=ppl), GpuFrame(W, H, N, tile, ppl=ppl), torch.zeros(8, device=DEV)
+    for _ in range(3):
+        _lib.fit_frame(f.shape, target, *fit, trace, f.ws, _lib.fit_opts(1, 1, cfg=cfg, qat=(8, 8)))
+        q = _lib.ptq(*ref[:3], 8, 8)
+        q = [q["xy"], q["chol"], q["rgb"]]
+        dl = r.forward(*q, target=target)[1]
+        g = [torch.empty_like(p) for p in q]
+        for a in range(0, N, 7):
+            b = min(N, a + 7)
+            s = GpuFrame(W, H, b - a, tile, ppl=ppl)
+            part = [p[a:b].contiguous() for p in q]
+            _lib.project_bin(s.shape, part[0], part[1], s.ws)
+            for x, y in zip(g, s.backward(part[2], dl)):
+                x[a:b] = y
+        _lib.adam_step(*ref[:3], *g, *ref[3:], cfg)
+    for k, x, y in zip(("xy", "chol", "rgb", "m", "v", "step"), fit, ref):
+        np.testing.assert_array_equal(host(x), host(y), err_msg=k)
+
+
+@pytest.mark.parametrize("tile,ppl", [(8, 1), (16, 2), (32, 1), (32, 2)])
+def test_quantisation_aware_sums_do_not_depend_on_the_frame_size(tile, ppl):
+    """The same Gaussians and pixels in a frame of 256x192 and in the corner
+    of one of 1024x768: the gradients differ by the factor 1/16 of the loss's
+    mean, a power of two, so with epsilon in that proportion 20 steps give the
+    same parameters and exactly scaled moments."""
+    print(f"qat frame size {tile}/{ppl}", flush=True)
+    xy, chol, rgb, frame = _one_sub_block_each(256, 192, ppl, 6)
+    large = np.zeros((3, 768, 1024), np.float32)
+    large[:, :192, :256] = frame
+    eps = float(np.float32(1e-8))
+    out = []
+    for T, e in ((frame, 16 * eps), (large, eps)):
+        f = GpuFrame(T.shape[2], T.shape[1], len(xy), tile, ppl=ppl)
+        s = _adam_start((xy, chol, rgb))
+        _lib.fit_frame(f.shape, dev(T), *s, torch.zeros(32, device=DEV), f.ws,
+                       _lib.fit_opts(20, 10, cfg=_lib.adam_cfg((2e-2, 5e-3, 5e-3), eps=e),
+                                     qat=(8, 8)))
+        out.append([host(x) for x in s])
+    for k, x, y, scale in zip(("xy", "chol", "rgb", "m", "v"), *out, (1, 1, 1, 16, 256)):
+        np.testing.assert_array_equal(x, y * np.float32(scale), err_msg=k)

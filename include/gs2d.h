@@ -262,7 +262,8 @@ int gs2d_select_changed(const gs2d_shape *shape, void *ws, size_t ws_bytes, cons
  * contraction: lo = min, hi = max, L = 2^b - 1, inv = L / (hi - lo) (0 if
  * hi == lo), step = (hi - lo) / L, code = clamp(rint((x - lo) inv), 0, L)
  * (ties to even), dequantised x^ = lo + code step.  Inputs must be finite.
- *   q_xy [N][2], q_chol [N][3], q_rgb [N][3]: dequantised parameters.
+ *   q_xy [N][2], q_chol [N][3], q_rgb [N][3]: dequantised parameters; each
+ *     may be the input it is the quantised form of (in place).
  *   codes (nullable) [N][8] uint16: binary16 bits of x, y, then the six codes.
  *   ranges (nullable) [6][2]: lo, hi of l1, l2, l3, r, g, b.
  *   bits (nullable) [7] double: N * H (empirical entropy of the codes, the

@@ -184,9 +184,23 @@ hipError_t launch_quantise(int N, const float *xy, const float *chol, const floa
   const hipError_t e = launch_quant_extremes(N, chol, rgb, qws, st);
   if (e != hipSuccess) return e;
   const int n_enc = std::min((N + QE - 1) / QE, Q_MAX_BLOCKS);
-  hipLaunchKernelGGL(k_q_encode, dim3(n_enc + (bits ? 6 : 0)), dim3(QE), 0, st, N, n_enc, q.blocks,
-                     xy, chol, rgb, bits_chol, bits_rgb, at<float>(qws, q.part), q_xy, q_chol,
-                     q_rgb, codes, ranges, bits, at<int>(qws, q.done));
+  auto encode = [&](int enc, int count) {
+    hipLaunchKernelGGL(k_q_encode, dim3(enc + count), dim3(QE), 0, st, N, enc, q.blocks, xy, chol,
+                       rgb, bits_chol, bits_rgb, at<float>(qws, q.part), q_xy, q_chol, q_rgb, codes,
+                       ranges, bits, at<int>(qws, q.done));
+  };
+  // In place, the components are counted before the encoder writes over them.
+  auto overlap = [N](const float *a, const float *b) {
+    return a < b + 3 * (size_t)N && b < a + 3 * (size_t)N;
+  };
+  const bool in_place = overlap(q_chol, chol) || overlap(q_chol, rgb) || overlap(q_rgb, chol) ||
+                        overlap(q_rgb, rgb);
+  if (bits && in_place) {
+    encode(0, 6);
+    encode(n_enc, 0);
+  } else {
+    encode(n_enc, bits ? 6 : 0);
+  }
   return hipGetLastError();
 }
 

@@ -213,3 +213,32 @@ def test_quantisation_aware_sums_do_not_depend_on_the_frame_size(tile, ppl):
         out.append([host(x) for x in s])
     for k, x, y, scale in zip(("xy", "chol", "rgb", "m", "v"), *out, (1, 1, 1, 16, 256)):
         np.testing.assert_array_equal(x, y * np.float32(scale), err_msg=k)
+
+
+@pytest.mark.parametrize("N", [700, 30000])
+@pytest.mark.parametrize("which", ["all", "chol", "rgb"])
+def test_ptq_in_place(N, which):
+    """Outputs written over the inputs: parameters, codes, ranges and bits
+    are those of a call with outputs of their own (bit for bit; the bits of
+    the oracle to FP64 rounding)."""
+    import ctypes
+    print(f"ptq in place N={N} {which}", flush=True)
+    src = [dev(p) for p in _gaussians(N, N + 3)]
+    ref = _lib.ptq(*src, 6, 7, want_codes=True)
+    p = [q.clone() for q in src]
+    out = [q if which in ("all", k) else torch.empty_like(q)
+           for q, k in zip(p, ("xy", "chol", "rgb"))]
+    codes = torch.empty(N, 8, dtype=torch.int16, device=DEV)
+    ranges, bits = torch.empty(6, 2, device=DEV), torch.empty(7, dtype=torch.float64, device=DEV)
+    need = _lib.lib().gs2d_ptq_workspace_bytes(N)
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    ptr = [ctypes.c_void_p(t.data_ptr()) for t in (*p, *out, codes, ranges, bits, ws)]
+    cfg = _lib.QuantCfg(6, 7)
+    assert _lib.lib().gs2d_ptq(N, *ptr[:3], ctypes.byref(cfg), *ptr[3:], need, _lib._stream()) == 0
+    for k, x in zip(("xy", "chol", "rgb"), out):
+        np.testing.assert_array_equal(host(x), host(ref[k]), err_msg=k)
+    np.testing.assert_array_equal(host(codes).astype(np.uint16), host(ref["codes"]))
+    np.testing.assert_array_equal(host(ranges), host(ref["ranges"]))
+    b = oracle_ptq(*[host(q) for q in src], 6, 7)
+    np.testing.assert_allclose(host(bits)[:6], b["component_bits"], rtol=1e-12, atol=1e-9)
+    assert abs(host(bits)[6] - b["bits"]) <= 1e-12 * b["bits"]

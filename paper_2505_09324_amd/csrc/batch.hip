@@ -310,10 +310,14 @@ struct BatchRaster {
   float *g_xy, *g_chol, *g_rgb;
 };
 
+// Chunks of 256 for every variant: a workgroup keeps its place for the whole
+// launch, so a list staged twice costs it more than fewer resident workgroups
+// do (20 frames of 96 x 64 / 1337 with 8 x 8 tiles, 5 iterations: 505 us, with
+// chunks of 64 916; 16 x 16 with 2 pixels per lane 618, with 128 786).
 template <int TILE, int PPL>
 __global__ void __launch_bounds__((Cfg<TILE, PPL>::NT)) GS2D_RASTER_OCCUPANCY
 k_b_render_persistent(BatchRaster a) {
-  using C = Cfg<TILE, PPL>;
+  using C = Cfg<TILE, PPL, 1, 1, 256>;
   __shared__ Smem<C> S;
   __shared__ float acc[C::CH * 8];
   __shared__ unsigned s_item;

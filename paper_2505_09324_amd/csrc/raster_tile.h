@@ -26,7 +26,7 @@ constexpr float INV_H15 = 1.6322368749392462f;        // (2 / log2(e))^1.5
 // (whole rows of sub-blocks, or part of one row); LS wavefronts share a
 // sub-block, each taking one of LS runs of its Gaussian list and exchanging
 // the forward sums through LDS.  Wavefront w: sub-block w % NB, run w / NB.
-template <int TILE, int PPL, int SPLIT = 1, int LS = 1>
+template <int TILE, int PPL, int SPLIT = 1, int LS = 1, int CHUNK = 0>
 struct Cfg {
   static constexpr int SBH = 8 * PPL;      // sub-block height (px)
   static constexpr int SBX = TILE / 8;     // sub-blocks per tile row
@@ -38,8 +38,8 @@ struct Cfg {
   // Gaussians staged per LDS chunk: fewer where a workgroup has only one or
   // two sub-blocks, so that the LDS of 32 wavefronts' workgroups fits one
   // compute unit (256 everywhere left 8 x 8 tiles 2 and 16 x 16 tiles with 2
-  // pixels per lane 4 of 8 wavefronts per SIMD).
-  static constexpr int CH = NWT == 1 ? 64 : NWT == 2 ? 128 : 256;
+  // pixels per lane 4 of 8 wavefronts per SIMD).  CHUNK: another choice.
+  static constexpr int CH = CHUNK ? CHUNK : NWT == 1 ? 64 : NWT == 2 ? 128 : 256;
   // floats the wavefronts of a sub-block exchange
   static constexpr int XCH = LS > 1 ? NW * 64 * PPL * 3 : 1;
   static_assert(SBY >= 1 && NWT <= 16, "unsupported tile / pixels-per-lane");

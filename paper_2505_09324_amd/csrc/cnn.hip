@@ -1576,9 +1576,12 @@ __device__ inline float target_mass(int n, const float *__restrict__ chol,
 // One wavefront per tile.  A bucket of at most 64 members with comparable
 // masses: every lane counts the members that come before its own.  Fuller
 // tiles, and a NaN mass (whose place depends on the order of insertion), take
-// the definition itself: all Gaussians in index order, the tile's inserted
-// one at a time, each replacing the lightest kept one (of equals the one with
-// the largest index) if it is heavier.  tcount: members in, targets out.
+// the definition itself: the tile's Gaussians in index order, inserted one at
+// a time, each replacing the lightest kept one (of equals the one with the
+// largest index) if it is heavier.  They come from the bucket or, where that
+// is full, from a pass over all Gaussians (1920x1080 / 30,000, every 50th
+// colour a NaN: 437 us with that pass for every tile with a NaN, 18 from the
+// buckets).  tcount: members in, targets out.
 constexpr int TARGET_BLOCK = 1024;
 __global__ void __launch_bounds__(TARGET_BLOCK)
 k_cnn_targets(int n_tiles, int N, int W, int H, int TX, int T, const float *__restrict__ xy,
@@ -1619,37 +1622,52 @@ k_cnn_targets(int n_tiles, int N, int W, int H, int TX, int T, const float *__re
       }
     } else {
       // lane s < k holds kept member s
-      int k = 0;
-      for (int b = 0; b < N; b += 64) {
-        const bool mem = b + lane < N && centre_tile(b + lane, W, H, TX, T, xy, chol) == t;
-        const float mm = mem ? target_mass(b + lane, chol, rgb) : 0.f;
-        for (unsigned long long bits = __ballot(mem); bits; bits &= bits - 1) {
-          const int j = __ffsll((long long)bits) - 1;
-          const float mj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mm), j));
-          int at = k;
-          if (k < NSLOT) {
-            ++k;
-          } else {
-            int worst = 0;
-            float wm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 0));
-            int wn = __builtin_amdgcn_readlane(n, 0);
-            for (int q = 1; q < NSLOT; ++q) {
-              const float qm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), q));
-              const int qn = __builtin_amdgcn_readlane(n, q);
-              if (qm < wm || (qm == wm && qn > wn)) {
-                worst = q;
-                wm = qm;
-                wn = qn;
-              }
+      int k = 0, kn = 0;
+      float km = 0.f;
+      auto insert = [&](int nj, float mj) {
+        int at = k;
+        if (k < NSLOT) {
+          ++k;
+        } else {
+          int worst = 0;
+          float wm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(km), 0));
+          int wn = __builtin_amdgcn_readlane(kn, 0);
+          for (int q = 1; q < NSLOT; ++q) {
+            const float qm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(km), q));
+            const int qn = __builtin_amdgcn_readlane(kn, q);
+            if (qm < wm || (qm == wm && qn > wn)) {
+              worst = q;
+              wm = qm;
+              wn = qn;
             }
-            at = mj > wm ? worst : -1;
           }
-          if (lane == at) {
-            n = b + j;
-            m = mj;
+          at = mj > wm ? worst : -1;
+        }
+        if (lane == at) {
+          kn = nj;
+          km = mj;
+        }
+      };
+      if (cnt <= BUCKET) {
+        int place = lane < cnt ? 0 : -1;  // of this lane's member in index order
+        for (int j = 0; j < cnt; ++j)
+          if (__builtin_amdgcn_readlane(n, j) < n && lane < cnt) ++place;
+        for (int i = 0; i < cnt; ++i) {
+          const int j = __ffsll((long long)__ballot(place == i)) - 1;
+          insert(__builtin_amdgcn_readlane(n, j),
+                 __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), j)));
+        }
+      } else {
+        for (int b = 0; b < N; b += 64) {
+          const bool mem = b + lane < N && centre_tile(b + lane, W, H, TX, T, xy, chol) == t;
+          const float mm = mem ? target_mass(b + lane, chol, rgb) : 0.f;
+          for (unsigned long long bits = __ballot(mem); bits; bits &= bits - 1) {
+            const int j = __ffsll((long long)bits) - 1;
+            insert(b + j, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mm), j)));
           }
         }
       }
+      n = kn;
       if (lane < k) slot = 0;
       for (int q = 0; q < k; ++q) {
         const int qn = __builtin_amdgcn_readlane(n, q);

@@ -1529,13 +1529,19 @@ k_pf_replace(int N, int n_tiles, int TX, const unsigned long long *__restrict__ 
 // (ties to the lower index), listed by increasing index.  The order of a
 // tile's members does not matter to a choice by (mass, index), so they are
 // not sorted: k_target_buckets appends each Gaussian to its tile's bucket,
-// which is the tile's own 64 words of the target vectors, and k_cnn_targets
-// reads a bucket into one wavefront, one member per lane, before it writes
-// the vectors over it.  (Sorting the Gaussians by tile and walking each list
+// which is the tile's own 64 words of the target vectors, or if that is full
+// to one list of the frame, and k_cnn_targets reads a bucket into one
+// wavefront, one member per lane, before it writes the vectors over it.
+// (Sorting the Gaussians by tile and walking each list
 // with one thread took 95 us in ten launches at 8160 tiles and 30,000
 // Gaussians.)
 constexpr int BUCKET = NSLOT * NPAR;
 static_assert(BUCKET == 64, "one bucket member per lane");
+
+// The Gaussians past a full bucket: *n entries (tile, Gaussian) in any order.
+struct TargetSpill {
+  int *n, *tile, *id;
+};
 
 // Tile of Gaussian n's centre, -1 outside the frame or for a degenerate one.
 __device__ inline int centre_tile(int n, int W, int H, int TX, int T, const float *__restrict__ xy,
@@ -1548,22 +1554,31 @@ __device__ inline int centre_tile(int n, int W, int H, int TX, int T, const floa
 }
 
 __global__ void __launch_bounds__(256)
-k_target_clear(int n_tiles, int *__restrict__ tcount, int *__restrict__ n_cd) {
+k_target_clear(int n_tiles, int *__restrict__ tcount, int *__restrict__ n_cd,
+               int *__restrict__ n_spill) {
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t < n_tiles) tcount[t] = 0;
-  if (t == 0) *n_cd = 0;
+  if (t == 0) *n_cd = *n_spill = 0;
 }
 
 __global__ void __launch_bounds__(256)
 k_target_buckets(int N, int W, int H, int TX, int T, const float *__restrict__ xy,
                  const float *__restrict__ chol, int *__restrict__ tcount,
-                 int *__restrict__ bucket) {
+                 int *__restrict__ bucket, TargetSpill spill) {
   const int n = blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  const int t = centre_tile(n, W, H, TX, T, xy, chol);
-  if (t < 0) return;
-  const int c = atomicAdd(&tcount[t], 1);
-  if (c < BUCKET) bucket[(size_t)t * BUCKET + c] = n;
+  const int t = n < N ? centre_tile(n, W, H, TX, T, xy, chol) : -1;
+  const int c = t >= 0 ? atomicAdd(&tcount[t], 1) : 0;
+  if (t >= 0 && c < BUCKET) bucket[(size_t)t * BUCKET + c] = n;
+  // the spilled of a wavefront take one run of the list
+  const unsigned long long out = __ballot(c >= BUCKET);
+  if (out == 0) return;
+  int at = 0;
+  if ((threadIdx.x & 63) == 0) at = atomicAdd(spill.n, __popcll(out));
+  at = __builtin_amdgcn_readfirstlane(at) + __popcll(out & lanemask_lt());
+  if (c >= BUCKET) {
+    spill.tile[at] = t;
+    spill.id[at] = n;
+  }
 }
 
 __device__ inline float target_mass(int n, const float *__restrict__ chol,
@@ -1573,20 +1588,100 @@ __device__ inline float target_mass(int n, const float *__restrict__ chol,
   return f32_mul(a, f32_add(f32_add(f32_mul(c0, c0), f32_mul(c1, c1)), f32_mul(c2, c2)));
 }
 
-// One wavefront per tile.  A bucket of at most 64 members with comparable
-// masses: every lane counts the members that come before its own.  Fuller
-// tiles, and a NaN mass (whose place depends on the order of insertion), take
-// the definition itself: the tile's Gaussians in index order, inserted one at
-// a time, each replacing the lightest kept one (of equals the one with the
-// largest index) if it is heavier.  They come from the bucket or, where that
-// is full, from a pass over all Gaussians (1920x1080 / 30,000, every 50th
-// colour a NaN: 437 us with that pass for every tile with a NaN, 18 from the
-// buckets).  tcount: members in, targets out.
+__device__ inline float lane_value(float x, int j) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));
+}
+
+// The kept members of a tile, by one wavefront: lane s < k holds member s.
+struct TargetKept {
+  int lane, k, n;
+  float m;
+  int worst, wn;  // the lightest (of equals the largest index): lane, Gaussian, mass
+  float wm;
+  __device__ void put(int at, int nj, float mj) {
+    if (lane == at) {
+      n = nj;
+      m = mj;
+    }
+  }
+  __device__ void find_lightest() {
+    worst = 0;
+    wm = lane_value(m, 0);
+    wn = __builtin_amdgcn_readlane(n, 0);
+    for (int q = 1; q < NSLOT; ++q) {
+      const float qm = lane_value(m, q);
+      const int qn = __builtin_amdgcn_readlane(n, q);
+      if (qm < wm || (qm == wm && qn > wn)) {
+        worst = q;
+        wm = qm;
+        wn = qn;
+      }
+    }
+  }
+  // The definition's step, for members in index order.
+  __device__ void insert(int nj, float mj) {
+    if (k < NSLOT) {
+      put(k++, nj, mj);
+    } else {
+      find_lightest();
+      if (mj > wm) put(worst, nj, mj);
+    }
+  }
+};
+
+// The spilled members of tile t among the kept ones (NSLOT of comparable
+// masses); false if one of theirs is a NaN.
+__device__ inline bool keep_spilled(TargetKept &K, int t, const TargetSpill &spill,
+                                    const float *__restrict__ chol,
+                                    const float *__restrict__ rgb) {
+  constexpr int BATCH = 8;  // entries per lane in flight
+  const int total = *spill.n;
+  K.find_lightest();
+  for (int b = K.lane; b - K.lane < total; b += 64 * BATCH) {
+    unsigned hits = 0;
+#pragma unroll
+    for (int q = 0; q < BATCH; ++q) {
+      const int e = spill.tile[min(b + 64 * q, total - 1)];
+      hits |= (b + 64 * q < total && e == t ? 1u : 0u) << q;
+    }
+    if (__ballot(hits != 0) == 0) continue;
+    for (int q = 0; q < BATCH; ++q) {
+      bool mem = (hits >> q) & 1;
+      if (__ballot(mem) == 0) continue;
+      const int n = mem ? spill.id[b + 64 * q] : 0;
+      const float m = mem ? target_mass(n, chol, rgb) : 0.f;
+      if (__ballot(m != m)) return false;
+      while (const unsigned long long in =
+                 __ballot(mem && (m > K.wm || (m == K.wm && n < K.wn)))) {
+        const int j = __ffsll((long long)in) - 1;
+        K.put(K.worst, __builtin_amdgcn_readlane(n, j), lane_value(m, j));
+        K.find_lightest();
+        if (K.lane == j) mem = false;
+      }
+    }
+  }
+  return true;
+}
+
+// One wavefront per tile.  With comparable masses every lane counts the members
+// of the bucket that come before its own.  A tile of more than 64 members goes
+// on with its part of the spilled list, read 512 entries at a time: nearly all
+// of a batch's members are lighter than the kept ones and fall out together
+// (1280x720 / 65,536 from the content-aware initialisation: 522 us with a pass
+// over all Gaussians for each such tile, 26 now; 640x360 / 65,536, 73 members a
+// tile: 613 and 63).  A NaN mass, whose place
+// depends on the order of insertion, takes the definition itself: the tile's
+// Gaussians in index order, inserted one at a time, each replacing the lightest
+// kept one (of equals the one with the largest index) if it is heavier.  They
+// come from the bucket or, where that is full, from a pass over all Gaussians
+// (1920x1080 / 30,000, every 50th colour a NaN: 437 us with that pass for every
+// tile with a NaN, 18 from the buckets).  tcount: members in, targets out.
 constexpr int TARGET_BLOCK = 1024;
 __global__ void __launch_bounds__(TARGET_BLOCK)
 k_cnn_targets(int n_tiles, int N, int W, int H, int TX, int T, const float *__restrict__ xy,
               const float *__restrict__ chol, const float *__restrict__ rgb,
-              int *__restrict__ tcount, float *__restrict__ tvec, int *__restrict__ n_cd) {
+              int *__restrict__ tcount, float *__restrict__ tvec, int *__restrict__ n_cd,
+              TargetSpill spill) {
   __shared__ int live;
   if (threadIdx.x == 0) live = 0;
   __syncthreads();
@@ -1598,21 +1693,19 @@ k_cnn_targets(int n_tiles, int N, int W, int H, int TX, int T, const float *__re
     float *out = tvec + (size_t)t * BUCKET;
     int n = 0, slot = -1;  // this lane's Gaussian and its place among the targets
     float m = 0.f;
-    bool in_order = cnt > BUCKET;
-    if (!in_order) {
-      if (lane < cnt) {
-        n = __float_as_int(out[lane]);  // as the stores below see it
-        m = target_mass(n, chol, rgb);
-      }
-      in_order = __ballot(m != m) != 0;
+    const int held = min(cnt, BUCKET);  // members in the bucket
+    if (lane < held) {
+      n = __float_as_int(out[lane]);  // as the stores below see it
+      m = target_mass(n, chol, rgb);
     }
-    if (!in_order) {
-      int rank = 0;
-      for (int j = 0; j < cnt; ++j) {
-        const float mj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), j));
-        const int nj = __builtin_amdgcn_readlane(n, j);
-        rank += (mj > m || (mj == m && nj < n)) ? 1 : 0;
-      }
+    bool in_order = __ballot(m != m) != 0;
+    int rank = 0;
+    for (int j = 0; j < held; ++j) {
+      const float mj = lane_value(m, j);
+      const int nj = __builtin_amdgcn_readlane(n, j);
+      rank += (mj > m || (mj == m && nj < n)) ? 1 : 0;
+    }
+    if (cnt <= BUCKET && !in_order) {
       const bool keep = lane < cnt && rank < NSLOT;
       const unsigned long long kept = __ballot(keep);
       if (keep) slot = 0;
@@ -1621,57 +1714,39 @@ k_cnn_targets(int n_tiles, int N, int W, int H, int TX, int T, const float *__re
         if (keep && ((kept >> j) & 1) && nj < n) ++slot;
       }
     } else {
-      // lane s < k holds kept member s
-      int k = 0, kn = 0;
-      float km = 0.f;
-      auto insert = [&](int nj, float mj) {
-        int at = k;
-        if (k < NSLOT) {
-          ++k;
-        } else {
-          int worst = 0;
-          float wm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(km), 0));
-          int wn = __builtin_amdgcn_readlane(kn, 0);
-          for (int q = 1; q < NSLOT; ++q) {
-            const float qm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(km), q));
-            const int qn = __builtin_amdgcn_readlane(kn, q);
-            if (qm < wm || (qm == wm && qn > wn)) {
-              worst = q;
-              wm = qm;
-              wn = qn;
-            }
-          }
-          at = mj > wm ? worst : -1;
+      TargetKept K = {};
+      K.lane = lane;
+      if (!in_order) {  // the bucket's heaviest, then the spilled members
+        for (; K.k < NSLOT; ++K.k) {
+          const int j = __ffsll((long long)__ballot(rank == K.k)) - 1;
+          K.put(K.k, __builtin_amdgcn_readlane(n, j), lane_value(m, j));
         }
-        if (lane == at) {
-          kn = nj;
-          km = mj;
-        }
-      };
-      if (cnt <= BUCKET) {
+        in_order = !keep_spilled(K, t, spill, chol, rgb);
+        if (in_order) K.k = 0;
+      }
+      if (in_order && cnt <= BUCKET) {
         int place = lane < cnt ? 0 : -1;  // of this lane's member in index order
         for (int j = 0; j < cnt; ++j)
           if (__builtin_amdgcn_readlane(n, j) < n && lane < cnt) ++place;
         for (int i = 0; i < cnt; ++i) {
           const int j = __ffsll((long long)__ballot(place == i)) - 1;
-          insert(__builtin_amdgcn_readlane(n, j),
-                 __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), j)));
+          K.insert(__builtin_amdgcn_readlane(n, j), lane_value(m, j));
         }
-      } else {
+      } else if (in_order) {
         for (int b = 0; b < N; b += 64) {
           const bool mem = b + lane < N && centre_tile(b + lane, W, H, TX, T, xy, chol) == t;
           const float mm = mem ? target_mass(b + lane, chol, rgb) : 0.f;
           for (unsigned long long bits = __ballot(mem); bits; bits &= bits - 1) {
             const int j = __ffsll((long long)bits) - 1;
-            insert(b + j, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mm), j)));
+            K.insert(b + j, lane_value(mm, j));
           }
         }
       }
-      n = kn;
-      if (lane < k) slot = 0;
-      for (int q = 0; q < k; ++q) {
+      n = K.n;
+      if (lane < K.k) slot = 0;
+      for (int q = 0; q < K.k; ++q) {
         const int qn = __builtin_amdgcn_readlane(n, q);
-        if (lane < k && qn < n) ++slot;
+        if (lane < K.k && qn < n) ++slot;
       }
     }
     const int k = min(cnt, NSLOT);
@@ -1828,7 +1903,8 @@ int gs2d_cnn_targets(int32_t H, int32_t W, int32_t N, const float *xy, const flo
   if (!cnn_layout(H, W, &C) || N < 1 || N > 65536 || !xy || !chol || !rgb || !ws || !scratch)
     return GS2D_EINVAL;
   if (ws_bytes < C.total) return GS2D_ENOSPACE;
-  // the scratch space this call asks for (its present form leaves it alone)
+  // scratch holds the spilled members (tile, Gaussian) and their number; the
+  // size asked for is that of the interface, which is larger
   const int G = std::max(1, std::min(SORT_MAX_BLOCKS, (N + 2047) / 2048));
   const size_t need = al256(4 * (size_t)N) * 2 + al256(4 * (size_t)RADIX * G) +
                       al256(4 * ((size_t)C.n_tiles + 1)) + 256;
@@ -1836,15 +1912,17 @@ int gs2d_cnn_targets(int32_t H, int32_t W, int32_t N, const float *xy, const flo
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   int *tcount = at<int>(ws, C.tcount), *ncd = at<int>(ws, C.ncd);
   float *tvec = at<float>(ws, C.tvec);
+  const TargetSpill spill{at<int>(scratch, 2 * al256(4 * (size_t)N)), at<int>(scratch, 0),
+                          at<int>(scratch, al256(4 * (size_t)N))};
   hipLaunchKernelGGL(k_target_clear, dim3((C.n_tiles + 255) / 256), dim3(256), 0, st, C.n_tiles,
-                     tcount, ncd);
+                     tcount, ncd, spill.n);
   hipLaunchKernelGGL(k_target_buckets, dim3((N + 255) / 256), dim3(256), 0, st, N, W, H, C.TX, 16,
-                     xy, chol, tcount, reinterpret_cast<int *>(tvec));
+                     xy, chol, tcount, reinterpret_cast<int *>(tvec), spill);
   // at most one block per compute unit: each adds once to the tile counter
   const int per = TARGET_BLOCK / 64;
   hipLaunchKernelGGL(k_cnn_targets, dim3(std::min((C.n_tiles + per - 1) / per, 256)),
                      dim3(TARGET_BLOCK), 0, st, C.n_tiles, N, W, H, C.TX, 16, xy, chol, rgb, tcount,
-                     tvec, ncd);
+                     tvec, ncd, spill);
   return hipGetLastError() == hipSuccess ? GS2D_OK : GS2D_EHIP;
 }
 

@@ -492,3 +492,62 @@ def test_targets_with_nan_masses_take_the_tile_lists():
         best[name] = min(best.get(name, 1e9), (time.perf_counter() - t0) / 20)
     print({k: f"{v * 1e6:.0f} us" for k, v in best.items()}, flush=True)
     assert best["nan"] < 4 * best["plain"]
+
+
+@pytest.mark.parametrize("nan", [False, True])
+@pytest.mark.parametrize("per_tile", [63, 64, 65, 128, 700])
+def test_targets_at_the_edge_of_a_bucket(per_tile, nan):
+    """Tiles with exactly `per_tile` members between emptier ones, in shuffled
+    index order; a third of the masses equal, so that ties between members of
+    the bucket and spilled ones go by the index."""
+    print(f"cnn targets {per_tile} per tile nan={nan}", flush=True)
+    Hf, Wf = 64, 160
+    full = [0, 3, 17, 22, 39]
+    tiles = np.concatenate([np.repeat(full, per_tile), np.repeat(np.arange(40), 5)])
+    tiles = tiles[np.concatenate([np.arange(len(full) * per_tile),
+                                  len(full) * per_tile
+                                  + np.flatnonzero(~np.isin(np.repeat(np.arange(40), 5), full))])]
+    rng = np.random.default_rng(per_tile)
+    tiles = rng.permutation(tiles)
+    N = len(tiles)
+    xy, chol, rgb = synth.random_gaussians(N, Wf, Hf, seed=18, scale_lo=0.6, scale_hi=3.0)
+    xy = np.stack([tiles % 10 * 16 + rng.uniform(0, 15.9, N),
+                   tiles // 10 * 16 + rng.uniform(0, 15.9, N)], 1).astype(np.float32)
+    chol[::3] = [3.0, 0.0, 3.0]
+    rgb[::3] = 2.0
+    if nan:
+        rgb[7::29, 1] = np.nan
+    net = _lib.CNNInit(Hf, Wf, seed=5)
+    net.set_targets(dev(xy), dev(chol), dev(rgb))
+    counts, vec = (host(t) for t in net.read_targets())
+    ref = _serial_targets(xy, chol, rgb, Wf, net.TX)
+    for t in range(net.TY * net.TX):
+        ids = ref.get(t, [])
+        assert counts[t] == len(ids), t
+        np.testing.assert_array_equal(vec[t, :len(ids), 5:], rgb[ids])
+        np.testing.assert_allclose(vec[t, :len(ids), 0],
+                                   (xy[ids, 0] - t % net.TX * 16) / 16, rtol=1e-5, atol=1e-6)
+        assert not vec[t, len(ids):].any()
+
+
+def test_targets_of_full_tiles_read_the_spilled_members():
+    """65,536 Gaussians on 640x480 (55 a tile, one tile in ten over 64) in
+    twice the time that they take on 1280x720 (18 a tile); a pass over all
+    of them for each full tile takes 28 times as long."""
+    import time
+    print("cnn targets full time", flush=True)
+    N, best = 65536, {}
+    u = np.random.default_rng(3).uniform(0, 1, (N, 2)).astype(np.float32)
+    _, chol, rgb = synth.random_gaussians(N, 640, 480, seed=19, scale_lo=0.6, scale_hi=3.0)
+    for Wf, Hf in ((1280, 720), (640, 480)) * 3:
+        net = _lib.CNNInit(Hf, Wf, seed=5)
+        P = [dev(u * np.float32([Wf, Hf])), dev(chol), dev(rgb)]
+        net.set_targets(*P)
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(20):
+            net.set_targets(*P)
+        torch.cuda.synchronize()
+        best[Wf] = min(best.get(Wf, 1e9), (time.perf_counter() - t0) / 20)
+    print({k: f"{v * 1e6:.0f} us" for k, v in best.items()}, flush=True)
+    assert best[640] < 6 * best[1280]

@@ -181,8 +181,8 @@ k_count_pairs(FrameArgs f, unsigned long long *__restrict__ out) {
       const int j = S.list[w][k];
       const float4 A = S.A[j], B = S.B[j];
       const float u1 = (pxc - A.x) * A.z;
-      const float u2 = ((pyc - A.y) - A.w * u1) * B.x;
-      n += (inside && u1 * u1 + u2 * u2 <= CUTOFF_QS) ? 1u : 0u;
+      const float u2 = pair_base(A, u1, pyc - A.y) * B.x;
+      n += (inside && pair_q<1>(u1, u1 * u1, u2) <= CUTOFF_QS) ? 1u : 0u;
     }
   }
   for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);

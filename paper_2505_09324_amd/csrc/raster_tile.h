@@ -306,8 +306,19 @@ __device__ inline void pixel_of_thread(int tx, int ty, int *px, int *py0, int pa
   *py0 = ty * TILE + (w / C::SBX) * C::SBH + (lane >> 3) * PPL;
 }
 
-// q' of a pixel.  The same expression, rounding for rounding, wherever a pair is
-// evaluated: the cutoff must hold for the same pixels in every pass and route.
+// q' of a (pixel, Gaussian) pair, each operation and its rounding written out
+// and nothing left to the compiler's contraction: in every pass and route with
+// the same pixels per lane the cutoff holds for the same pixels.  A lane's
+// first row starts from base = dy - l2 u1; the rows below add 1/l3 to u2.  One
+// pixel per lane and several round the last step differently (they share
+// u1^2), so two such variants may differ on a pixel whose q' is within a few
+// ulp of the cutoff.
+__device__ __forceinline__ float pair_base(const float4 &A, float u1, float dy) {
+  return __builtin_fmaf(-A.w, u1, dy);
+}
+__device__ __forceinline__ float pair_next_row(int r, float base, float u2, float inv_l3) {
+  return r == 0 ? __builtin_fmaf(base, inv_l3, inv_l3) : u2 + inv_l3;
+}
 template <int PPL>
 __device__ __forceinline__ float pair_q(float u1, float u1s, float u2) {
   return PPL == 1 ? __builtin_fmaf(u1, u1, u2 * u2) : __builtin_fmaf(u2, u2, u1s);
@@ -328,11 +339,11 @@ __device__ inline int fwd_chunk(Smem<C> &S, int beg, int end, float pxc, float p
     const float4 A = S.A[j], B = S.B[j];
     const float u1 = (pxc - A.x) * A.z;
     const float u1s = u1 * u1;
-    const float base = (pyc0 - A.y) - A.w * u1;
+    const float base = pair_base(A, u1, pyc0 - A.y);
     bool any = false;
-    float u2 = base * B.x;  // the next pixel row adds 1/l3 (staged units)
+    float u2 = base * B.x;
 #pragma unroll
-    for (int r = 0; r < PPL; ++r, u2 += B.x) {
+    for (int r = 0; r < PPL; u2 = pair_next_row(r, base, u2, B.x), ++r) {
       const float q = pair_q<PPL>(u1, u1s, u2);
       const float e = __builtin_amdgcn_exp2f(-q);
       const bool in_cut = q <= CUTOFF_QS;
@@ -401,9 +412,9 @@ template <int PPL, bool CHECK_HITS, int N>
 __device__ __forceinline__ void batch_pixels(BatchSums &T, float &t0, float &t2, const float4 &B,
                                              float cut, float u1, float u1s, float base,
                                              const float (&g)[PPL][3]) {
-  float u2 = base * B.x;  // the next pixel row adds 1/l3
+  float u2 = base * B.x;
 #pragma unroll
-  for (int r = 0; r < PPL; ++r, u2 += B.x) {
+  for (int r = 0; r < PPL; u2 = pair_next_row(r, base, u2, B.x), ++r) {
     const float q = pair_q<PPL>(u1, u1s, u2);
     const float e = __builtin_amdgcn_exp2f(-q);
     const bool in_cut = q <= cut;
@@ -423,8 +434,9 @@ __device__ __forceinline__ void batch_column(BatchSums &T, const float4 &A, cons
   const float u1 = ((x0 + (float)COL) - A.x) * A.z;
   const float u1s = u1 * u1;
   float t0 = 0.f, t2 = 0.f;
-  batch_pixels<PPL, CHECK_HITS, COL>(T, t0, t2, B, cut, u1, u1s, yb[0] - A.w * u1, g);
-  batch_pixels<PPL, CHECK_HITS, COL + 8>(T, t0, t2, B, cut, u1, u1s, yb[1] - A.w * u1, g);
+  batch_pixels<PPL, CHECK_HITS, COL>(T, t0, t2, B, cut, u1, u1s, pair_base(A, u1, yb[0]),
+                                     g);
+  batch_pixels<PPL, CHECK_HITS, COL + 8>(T, t0, t2, B, cut, u1, u1s, pair_base(A, u1, yb[1]), g);
   t2 *= B.x;
   const float s1 = u1 * t0 - A.w * t2;
   T.v[0] += s1;
@@ -512,12 +524,12 @@ __device__ inline void bwd_chunk(const Smem<C> &S, float *acc, int beg, int end,
     const float4 A = S.A[j], B = S.B[j];
     const float u1 = (pxc - A.x) * A.z;
     const float u1s = u1 * u1;
-    const float base = (pyc0 - A.y) - A.w * u1;
+    const float base = pair_base(A, u1, pyc0 - A.y);
     float u2[PPL], q[PPL];
     bool any = false;
 #pragma unroll
     for (int r = 0; r < PPL; ++r) {
-      u2[r] = r == 0 ? base * B.x : u2[r - 1] + B.x;  // the next pixel row adds 1/l3
+      u2[r] = r == 0 ? base * B.x : pair_next_row(r - 1, base, u2[r - 1], B.x);
       q[r] = pair_q<PPL>(u1, u1s, u2[r]);
       any |= q[r] <= CUTOFF_QS;
     }

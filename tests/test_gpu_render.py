@@ -354,3 +354,32 @@ def test_every_route_at_frame_sizes(W, H):
             assert abs(float(x) - want_loss) <= tol, (float(x), want_loss, tol)
         for grads in (g, b):
             assert_grads_close(dict(zip(("xy", "chol", "rgb"), map(host, grads))), want)
+
+
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_counted_pairs_are_the_rendered_ones(tile):
+    """One Gaussian per 16x16 block with its cutoff through the centre of a
+    pixel (q = 9 there to a few roundings), colour 1: the pixels with a value
+    are the pairs that count_pairs finds, to the last borderline one."""
+    print(f"counted pairs tile={tile}", flush=True)
+    W, H = 1280, 720
+    rng = np.random.default_rng(11)
+    c = np.arange((W // 16) * (H // 16))
+    xy = np.stack([c % (W // 16) * 16 + 8 + rng.uniform(-1, 1, len(c)),
+                   c // (W // 16) * 16 + 8 + rng.uniform(-1, 1, len(c))], 1).astype(np.float32)
+    px = np.floor(xy) + 0.5 + rng.integers(-3, 4, xy.shape)
+    d = px - xy.astype(np.float64)
+    l2 = rng.uniform(-0.3, 0.3, len(c))
+    l1 = rng.uniform(1.0, 1.3, len(c))
+    # l3 for q = 9 at (dx, dy); where that is no Gaussian of the block, a round one
+    l3 = np.abs(d[:, 1] - l2 * d[:, 0] / l1) / np.sqrt(np.maximum(9 - (d[:, 0] / l1) ** 2, 1e-3))
+    round_ = (l3 < 0.3) | (l3 > 1.4)
+    l2[round_], l1[round_] = 0.0, np.hypot(d[round_, 0], d[round_, 1]) / 3
+    l3[round_] = l1[round_]
+    chol = np.stack([l1, l2, l3], 1).astype(np.float32)
+    N = len(c)
+    f = GpuFrame(W, H, N, tile)
+    img, _, _ = f.forward(dev(xy), dev(chol), torch.ones(N, 3, device="cuda"))
+    pairs = _lib.count_pairs(f.shape, f.ws)
+    assert pairs > 20 * N
+    assert int((img[0] != 0).sum()) == pairs

@@ -383,3 +383,56 @@ def test_counted_pairs_are_the_rendered_ones(tile):
     pairs = _lib.count_pairs(f.shape, f.ws)
     assert pairs > 20 * N
     assert int((img[0] != 0).sum()) == pairs
+
+
+# size -> variants rendered at it; together every (variant, share) pair of the
+# raster: four, two or one wavefront on a sub-block
+ROUTES = {
+    (320, 240): VARIANTS,
+    (480, 400): [(8, 1), (16, 1), (32, 1)],
+    (640, 480): VARIANTS[:5],
+    (960, 720): [(16, 2), (32, 2), (32, 4)],
+    (1100, 1000): [(32, 4)],
+}
+
+
+@pytest.mark.parametrize("W,H", ROUTES)
+def test_every_variant_with_every_share(W, H):
+    """As the frames above, at the sizes of ROUTES; the rule that picks the
+    share is read from the source, and the pairs visited must be complete."""
+    import pathlib
+    import re
+    src = pathlib.Path(_lib.HERE, "csrc", "raster_tile.h").read_text()
+    four, two = map(int, re.search(r"sub_blocks <= (\d+) \? 4 : sub_blocks <= (\d+) \? 2 : 1",
+                                   src).groups())
+
+    def share(w, h, T, ppl):
+        n = -(-w // T) * -(-h // T) * (T // 8) * (T // (8 * ppl))
+        return 4 if n <= four else 2 if n <= two else 1
+
+    visited = {(v, share(w, h, *v)) for (w, h), vs in ROUTES.items() for v in vs}
+    assert visited == {(v, s) for v in VARIANTS for s in (4, 2, 1)}
+    N = 1500
+    xy, chol, rgb = synth.random_gaussians(N, W, H, seed=61, scale_lo=1.0, scale_hi=8.0)
+    xy[:800] = 20.0 + xy[:800] * (40.0 / W)
+    chol[:, 1] = np.random.default_rng(62).uniform(-3, 3, N).astype(np.float32)
+    rgb -= 0.5
+    frame, _ = synth.make_frame(W, H, seed=63)
+    ref = render_box(xy, chol, rgb, H, W)
+    want_loss, tol = mse(ref["img"], frame), loss_bound(ref, frame)
+    dl = dloss_dimg(ref["img"], frame)
+    want = gradients(xy, chol, rgb, dl, H, W)
+    P = [dev(xy), dev(chol), dev(rgb)]
+    for T, ppl in ROUTES[W, H]:
+        print(f"shares {W}x{H} T={T} ppl={ppl} share={share(W, H, T, ppl)}", flush=True)
+        f = GpuFrame(W, H, N, T, max_pairs=400000, ppl=ppl)
+        img, _, loss = f.forward(*P, dev(frame))
+        assert_pixels_close(host(img), ref, what=f"T={T} ppl={ppl}")
+        g = [torch.zeros(N, d, device="cuda") for d in (2, 3, 3)]
+        floss = torch.empty((), device="cuda")
+        _lib.render_fused(f.shape, f.ws, P[2], dev(frame), *g, loss=floss)
+        b = f.backward(P[2], dev(dl.astype(np.float32)))
+        for x in (loss, floss):
+            assert abs(float(x) - want_loss) <= tol, (float(x), want_loss, tol)
+        for grads in (g, b):
+            assert_grads_close(dict(zip(("xy", "chol", "rgb"), map(host, grads))), want)

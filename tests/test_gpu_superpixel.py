@@ -184,3 +184,36 @@ def test_superpixel_full_hd():
     np.testing.assert_array_equal(gx, ox)
     np.testing.assert_array_equal(gc, oc)
     np.testing.assert_array_equal(gr, orgb)
+
+
+@pytest.mark.parametrize("K,piled", [(1400, False), (630, False), (630, True), (40, False)])
+def test_large_frame_with_a_small_roi(K, piled):
+    """1931x1003: two pixels per thread, ragged on the right and below.  The
+    ROI is a block across four tiles and the last corner; S = 1 (1400 seeds:
+    windows of more than 256 centres), 2 and 8, and with four fifths of the
+    seeds piled on a tenth of the pixels.  Two rounds against the oracle, and
+    the same without labels, when the last round only visits the ROI's tiles."""
+    print(f"superpixel large frame K={K} piled={piled}", flush=True)
+    W, H = 1931, 1003
+    frame, _ = synth.make_frame(W, H, seed=77)
+    mask = np.zeros((H, W), bool)
+    mask[83:127, 84:140] = True
+    mask[H - 9:, W - 13:] = True
+    ys, xs = np.nonzero(mask)
+    rng = np.random.default_rng(K + piled)
+    pick = rng.choice(len(xs), K, replace=piled)
+    if piled:
+        pick[:K * 4 // 5] = rng.integers(0, len(xs) // 10, K * 4 // 5)
+    seeds = (ys[pick] * W + xs[pick]).astype(np.int32)
+    fb = (rng.normal(0, 1, (K, 2)).astype(F32), np.ones((K, 3), F32),
+          rng.normal(0, 1, (K, 3)).astype(F32))
+    S = grid_step(int(mask.sum()), K)
+    assert S == {1400: 1, 630: 2, 40: 8}[K]
+    _compare_whole(frame, mask, seeds, fb, 2, 0.1)
+    _, cen, gx, gc, gr = _gpu(frame, mask, seeds, fb, 2, 0.1)
+    P = [dev(a) for a in fb]
+    centres = torch.zeros(2, 5, K, device=DEV)
+    _lib.init_superpixel(dev(frame), dev(mask.astype(np.uint8)), dev(seeds), *P, iters=2,
+                         compactness=0.1, centres=centres)
+    for got, want in zip((centres, *P), (cen, gx, gc, gr)):
+        np.testing.assert_array_equal(host(got), want)

@@ -551,3 +551,60 @@ def test_targets_of_full_tiles_read_the_spilled_members():
         best[Wf] = min(best.get(Wf, 1e9), (time.perf_counter() - t0) / 20)
     print({k: f"{v * 1e6:.0f} us" for k, v in best.items()}, flush=True)
     assert best[640] < 6 * best[1280]
+
+
+def _conv_passes(x, w, b, dy, stride):
+    """(y, dx, dw) of conv3x3 and its backward as FP64 matrix products."""
+    (C, h, v), (O, ho, wo) = x.shape, dy.shape
+    xp = np.zeros((C, h + 2, v + 2))
+    xp[:, 1:-1, 1:-1] = x
+    y, dxp, dw = np.zeros((O, ho * wo)) + b[:, None], np.zeros_like(xp), np.zeros_like(w)
+    d = np.ascontiguousarray(dy.reshape(O, -1))
+    for i in range(3):
+        for j in range(3):
+            sl = (slice(None), slice(i, i + stride * (ho - 1) + 1, stride),
+                  slice(j, j + stride * (wo - 1) + 1, stride))
+            p = xp[sl].reshape(C, -1)
+            y += w[:, :, i, j] @ p
+            dw[:, :, i, j] = d @ p.T
+            dxp[sl] += (w[:, :, i, j].T @ d).reshape(C, ho, wo)
+    return y.reshape(O, ho, wo), dxp[:, 1:-1, 1:-1], dw
+
+
+def test_layers_of_a_frame_of_many_tiles():
+    """1040x1000: 1056 tiles of layer 1's gradient on 512 workgroups and 13
+    tiles per grad-weight workgroup, so every workgroup goes round its LDS
+    buffers.  Every element of the forward passes, of dZ and of the weight
+    and bias gradients against FP64 products of the GPU's own BF16 tensors,
+    with the bounds of the element-wise test above."""
+    print("cnn layers of many tiles", flush=True)
+    H, W = 1040, 1000
+    f0, f1 = _frames(71, (H, W))
+    xy, chol, rgb = synth.random_gaussians(6000, W, H, seed=72, scale_lo=0.6, scale_hi=3.0)
+    net = _lib.CNNInit(H, W, seed=73)
+    net.set_targets(dev(xy), dev(chol), dev(rgb))
+    head = torch.empty(73, net.TY, net.TX, device=DEV)
+    net.forward(dev(f1), dev(f0), head_out=head)
+    net.backward()
+    torch.cuda.synchronize()
+    params, grads, hd = net.oracle_params(), net.oracle_grads(), host(head).astype(np.float64)
+    X = [net.tensor(i, 0).astype(np.float64) for i in range(5)]
+    X[0] = X[0][:6]
+    for i, (w, b) in enumerate(params):
+        wq, stride = ocnn.bf16_round(w).astype(np.float64), 2 if i < 4 else 1
+        b = np.asarray(b, np.float64)
+        DZ = net.tensor(i, 1)[:73 if i == 4 else 64].astype(np.float64)
+        y, dx, dw = _conv_passes(X[i], wq, b, DZ, stride)
+        ay, adx, adw = _conv_passes(np.abs(X[i]), np.abs(wq), np.abs(b), np.abs(DZ), stride)
+        if i < 4:
+            _close_bf16(X[i + 1], np.maximum(y, 0.0), 1e-3 * ay, f"forward layer {i}")
+        else:
+            assert np.all(np.abs(hd - y) <= 1e-3 * ay + 1e-30), "head"
+        gw, gb = grads[i]
+        assert np.all(np.abs(gw - dw) <= 1e-3 * adw + 1e-30), f"grad weight {i}"
+        assert np.all(np.abs(gb - DZ.sum((1, 2))) <= 1e-3 * np.abs(DZ).sum((1, 2)) + 1e-30), i
+        if i > 0:
+            mask = X[i] > 0
+            got = net.tensor(i - 1, 1)[:64]
+            assert not got[~mask].any(), f"grad input {i}: masked entries not zero"
+            _close_bf16(got[mask], dx[mask], 1e-3 * adx[mask], f"grad input into layer {i}")

@@ -54,8 +54,8 @@ struct Cfg {
 // slowest wavefront is done, so smaller ones leave a shorter tail at the end
 // of a launch and fewer idle wavefronts before each barrier, at the price of
 // staging the tile's list once per part.  Fits of 20 iterations at 1920x1080 /
-// 30,000, us: 32/2 (8 sub-blocks) whole 1202, halves 1126, quarters 1208; 32/1
-// (16) whole 1284, halves 1300, quarters 1200; halves of 16/1 2301 against 1971,
+// 30,000, us: 32/2 (8 sub-blocks) whole 1144, halves 1107, quarters 1191; 32/1
+// (16) whole 1277, halves 1223, quarters 1197; halves of 16/1 2301 against 1971,
 // of 16/2 2136 against 1854, of 32/4 no gain.
 #define GS2D_VARIANTS(X) \
   X(8, 1, 1, 1) X(16, 1, 1, 1) X(16, 2, 1, 1) X(32, 1, 4, 4) X(32, 2, 2, 4) X(32, 4, 1, 2)
@@ -66,7 +66,10 @@ struct Cfg {
 // 480x270 / 1200 (32/2: 1080 sub-blocks) alone 22.4, four 19.2; 640x360 / 1000
 // (1920) 20.5, 19.1; 800x450 / 4500 (3000) alone 27.4, two 25.6, four 28.5;
 // 640x360 with 16/1 (3680) 21.9, 20.9, 24.6; 960x540 / 7000 (4080) 28.4, 30.0,
-// 32.0; at 1280x720 (7360) two take 38.5 against 34.3.
+// 32.0; at 1280x720 (7360) two take 38.5 against 34.3.  The separate forward and
+// backward follow the same lines: 480x270 / 1200 alone 4.8 and 8.9 us, four 4.4
+// and 8.5; 800x450 / 4500 6.7 and 12.2, two 6.6 and 13.1; 640x360 with 16/1 4.7
+// and 10.0, two 5.1 and 9.7; 960x540 / 7000 7.1 and 12.6, two 7.8 and 17.2.
 inline int raster_share(long long sub_blocks) {
   return sub_blocks <= 2048 ? 4 : sub_blocks <= 3840 ? 2 : 1;
 }
@@ -599,7 +602,7 @@ __device__ inline void flush_grads(const Smem<C> &S, const float *acc, int cnt,
 }
 
 // Wavefront sum of one float per lane; lane 0 writes it to *slot.  Loss
-// partials are kept per wavefront (tile t, wavefront w at t * NW + w), so a
+// partials are kept per sub-block (tile t, sub-block b at t * NWT + b), so a
 // wavefront never waits for the rest of its tile to record its loss.
 __device__ inline void wave_loss(float v, float *__restrict__ slot) {
   v += dpp<DPP_QUAD_XOR1>(v);

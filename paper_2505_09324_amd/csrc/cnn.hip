@@ -87,11 +87,11 @@ constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, size_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (uint32_t)bytes, 0x00020000);
 }
-__device__ __forceinline__ uint4 load16(__amdgpu_buffer_rsrc_t b, uint32_t off, int base) {
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, base, 0));
+__device__ __forceinline__ uint4 load16(__amdgpu_buffer_rsrc_t b, uint32_t off, uint32_t base) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, (int)base, 0));
 }
-__device__ __forceinline__ float load4(__amdgpu_buffer_rsrc_t b, uint32_t off, int base) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, base, 0));
+__device__ __forceinline__ float load4(__amdgpu_buffer_rsrc_t b, uint32_t off, uint32_t base) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, (int)base, 0));
 }
 
 // --------------------------------------------------------------- forward --
@@ -587,7 +587,9 @@ __device__ __forceinline__ void gw_layer(const GwLayer &L, int work, uint8_t *ld
   auto load = [&](Stage &v, int t) {
     const int oy0 = t / L.tiles_x * 8, ox0 = t % L.tiles_x * 8;
     const int iy0 = oy0 * S - 1, ix0 = ox0 * S - 1;
-    const int xbase = (iy0 * L.Win + ix0) * 128, zbase = (oy0 * L.Wout + ox0) * L.CoutS * 2;
+    // unsigned: the second layer's input of the largest frames passes 2^31 bytes
+    const uint32_t xbase = (uint32_t)(iy0 * L.Win + ix0) * 128u;
+    const uint32_t zbase = (uint32_t)(oy0 * L.Wout + ox0) * (uint32_t)L.CoutS * 2u;
     if (iy0 >= 0 && ix0 >= 0 && iy0 + PW <= L.Hin && ix0 + PW <= L.Win) {  // also within dZ
 #pragma unroll
       for (int j = 0; j < PER; ++j) v.x[j] = load16(xs, fx[j], xbase);
